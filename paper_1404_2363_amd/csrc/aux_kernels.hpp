@@ -66,20 +66,27 @@ LBM_FORCEINLINE double ld_pop(const void* p, int64_t i, double inv) {
 }
 
 // phi of one node and the number of non-finite stored values there.  Split
-// storage keeps phi itself; otherwise phi = sum_i f_i (+ phi_ref).
-template <typename S>
-LBM_FORCEINLINE double node_phi(const RunArgs& a, int Q, int64_t node, int& nonfinite) {
+// storage keeps phi itself; otherwise phi = sum_i f_i (+ phi_ref).  Q is a
+// template argument so that the Q loads of a node are all in flight before
+// the first addition: with the count known only at run time each load waited
+// for the one before it (Sum phi, x-moments, non-finite count and phi of a
+// 2048^2 D2Q9 FP32 state: 336 us, with the count unrolled 191 us).
+template <typename S, int Q>
+LBM_FORCEINLINE double node_phi(const RunArgs& a, int64_t node, int& nonfinite) {
   if (a.src_phi) {
     const double phi = (double)((const float*)a.src_phi)[node];
     nonfinite += !isfinite(phi);
+#pragma unroll
     for (int i = 0; i < Q; ++i) nonfinite += !isfinite(ld_pop<S>(a.src, i * a.plane + node, 1.0));
     return phi;
   }
-  double s = 0.0;
+  double v[Q], s = 0.0;
+#pragma unroll
+  for (int i = 0; i < Q; ++i) v[i] = ld_pop<S>(a.src, i * a.plane + node, a.fp16_inv_scale);
+#pragma unroll
   for (int i = 0; i < Q; ++i) {
-    const double v = ld_pop<S>(a.src, i * a.plane + node, a.fp16_inv_scale);
-    nonfinite += !isfinite(v);
-    s += v;
+    nonfinite += !isfinite(v[i]);
+    s += v[i];
   }
   return s + a.phi_ref;
 }
@@ -101,32 +108,34 @@ LBM_FORCEINLINE double plate_weight(const RunArgs& a, int64_t node) {
 }
 
 // phi = sum_i f_i (+ phi_ref for shifted storage), FP64.
-template <typename S>
-__global__ __launch_bounds__(256) void k_moments(const RunArgs a, int Q, double* __restrict__ phi) {
+template <typename S, int Q>
+__global__ __launch_bounds__(256) void k_moments(const RunArgs a, double* __restrict__ phi) {
   const int64_t N = a.nx * a.ny * a.nz;
   const int64_t node = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (node >= N) return;
   int bad = 0;
-  phi[node] = node_phi<S>(a, Q, node, bad);
+  phi[node] = node_phi<S, Q>(a, node, bad);
 }
 
 // Deterministic two-pass FP64 reduction.  Pass 1: each of RED_BLOCKS blocks
 // walks a fixed grid-stride set of nodes and tree-reduces 4 sums in LDS.
 // Pass 2: one block adds the partials in a fixed tree.
-template <typename S>
-__global__ __launch_bounds__(RED_THREADS) void k_reduce_partial(const RunArgs a, int Q, int kind, double x_ref,
+template <typename S, int Q>
+__global__ __launch_bounds__(RED_THREADS) void k_reduce_partial(const RunArgs a, int kind, double x_ref,
                                                                double* __restrict__ partial) {
   __shared__ double sh[4][RED_THREADS];
   const int64_t N = a.nx * a.ny * a.nz;
   double s0 = 0.0, s1 = 0.0, s2 = 0.0, bad = 0.0;
   const double nxd = (double)a.nx;
-  for (int64_t node = (int64_t)blockIdx.x * RED_THREADS + threadIdx.x; node < N;
-       node += (int64_t)gridDim.x * RED_THREADS) {
+  const int64_t stride = (int64_t)gridDim.x * RED_THREADS, first = (int64_t)blockIdx.x * RED_THREADS + threadIdx.x;
+  const int64_t dx = stride % a.nx;
+  int64_t x = first % a.nx;  // column of `node`, carried from pass to pass without a division
+  for (int64_t node = first; node < N; node += stride) {
     int nonfinite = 0;
-    const double phi = node_phi<S>(a, Q, node, nonfinite) * plate_weight(a, node);
+    const double phi = node_phi<S, Q>(a, node, nonfinite) * plate_weight(a, node);
     bad += (double)nonfinite;
     if (kind == LBM_CDE_RED_XMOMENTS) {
-      double d = (double)(node % a.nx) - x_ref;
+      double d = (double)x - x_ref;
       d -= nxd * floor(d / nxd + 0.5);
       s0 += phi;
       s1 += d * phi;
@@ -134,6 +143,8 @@ __global__ __launch_bounds__(RED_THREADS) void k_reduce_partial(const RunArgs a,
     } else {
       s0 += phi;
     }
+    x += dx;
+    if (x >= a.nx) x -= a.nx;
   }
   sh[0][threadIdx.x] = s0;
   sh[1][threadIdx.x] = s1;
@@ -172,8 +183,8 @@ LBM_FORCEINLINE int64_t run_steps(const RunArgs& a, int64_t t) {
 
 // Batched x-moments, pass 1: block (b, r) reduces part of run r (S0, S1, S2
 // about x_ref(t_r) = xref0 + xref_drift t_r of that run) into partial[r][b].
-template <typename R>
-__global__ __launch_bounds__(RED_THREADS) void k_batch_xmom_partial(const RunArgs* __restrict__ runs, int Q,
+template <typename R, int Q>
+__global__ __launch_bounds__(RED_THREADS) void k_batch_xmom_partial(const RunArgs* __restrict__ runs,
                                                                    const int64_t* __restrict__ clock,
                                                                    double* __restrict__ partial) {
   __shared__ double sh[3][RED_THREADS];
@@ -185,12 +196,20 @@ __global__ __launch_bounds__(RED_THREADS) void k_batch_xmom_partial(const RunArg
   x_ref -= nxd * floor(x_ref / nxd);
   const int64_t N = a.nx * a.ny * a.nz;
   double s0 = 0.0, s1 = 0.0, s2 = 0.0;
-  for (int64_t node = (int64_t)blockIdx.x * RED_THREADS + threadIdx.x; node < N;
-       node += (int64_t)gridDim.x * RED_THREADS) {
+  const int64_t stride = (int64_t)gridDim.x * RED_THREADS, first = (int64_t)blockIdx.x * RED_THREADS + threadIdx.x;
+  const int64_t dx = stride % a.nx;
+  int64_t x = first % a.nx;
+  for (int64_t node = first; node < N; node += stride) {
+    R v[Q];
+#pragma unroll
+    for (int i = 0; i < Q; ++i) v[i] = src[i * a.plane + node];
     double phi = 0.0;
-    for (int i = 0; i < Q; ++i) phi += (double)src[i * a.plane + node];
+#pragma unroll
+    for (int i = 0; i < Q; ++i) phi += (double)v[i];
     phi = (phi + a.phi_ref) * plate_weight(a, node);
-    double d = (double)(node % a.nx) - x_ref;
+    double d = (double)x - x_ref;
+    x += dx;
+    if (x >= a.nx) x -= a.nx;
     d -= nxd * floor(d / nxd + 0.5);
     s0 += phi;
     s1 += d * phi;

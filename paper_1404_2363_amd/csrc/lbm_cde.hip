@@ -900,17 +900,20 @@ void launch_init(const Run& r, const RunArgs& a, const double* phi0, hipStream_t
   else hipLaunchKernelGGL(k_init_d3q15<R>, dim3(blocks), dim3(256), 0, s, a, phi0);
 }
 
+// Pass 1 of a reduction of run r's current state: nb partials.
+void launch_reduce_partial(const lbm_cde* h, const Run& r, const RunArgs& a, int kind, double x_ref, unsigned nb,
+                           double* partial) {
+  const dim3 g(nb), b(RED_THREADS);
+  hipStream_t s = h->stream;
+  if (r.half) hipLaunchKernelGGL((k_reduce_partial<__half, 9>), g, b, 0, s, a, kind, x_ref, partial);
+  else if (r.dbl && r.Q == 9) hipLaunchKernelGGL((k_reduce_partial<double, 9>), g, b, 0, s, a, kind, x_ref, partial);
+  else if (r.dbl) hipLaunchKernelGGL((k_reduce_partial<double, 15>), g, b, 0, s, a, kind, x_ref, partial);
+  else if (r.Q == 9) hipLaunchKernelGGL((k_reduce_partial<float, 9>), g, b, 0, s, a, kind, x_ref, partial);
+  else hipLaunchKernelGGL((k_reduce_partial<float, 15>), g, b, 0, s, a, kind, x_ref, partial);
+}
+
 int reduce_into(lbm_cde* h, Run& r, int kind, double x_ref, double* out_dev) {
-  RunArgs a = make_args(h, r, r.cur);
-  if (r.dbl)
-    hipLaunchKernelGGL(k_reduce_partial<double>, dim3(RED_BLOCKS), dim3(RED_THREADS), 0, h->stream, a, r.Q, kind,
-                       x_ref, r.red_partial);
-  else if (r.half)
-    hipLaunchKernelGGL(k_reduce_partial<__half>, dim3(RED_BLOCKS), dim3(RED_THREADS), 0, h->stream, a, r.Q, kind,
-                       x_ref, r.red_partial);
-  else
-    hipLaunchKernelGGL(k_reduce_partial<float>, dim3(RED_BLOCKS), dim3(RED_THREADS), 0, h->stream, a, r.Q, kind,
-                       x_ref, r.red_partial);
+  launch_reduce_partial(h, r, make_args(h, r, r.cur), kind, x_ref, RED_BLOCKS, r.red_partial);
   hipLaunchKernelGGL(k_reduce_final, dim3(1), dim3(RED_THREADS), 0, h->stream, r.red_partial, RED_BLOCKS, out_dev);
   HIP_TRY(h, hipGetLastError());
   return LBM_CDE_OK;
@@ -1431,14 +1434,13 @@ void launch_batch_step(lbm_cde* h, hipStream_t s, unsigned grid) {
 
 // Sample the x-moments of every run into hist[row], then advance the row clock.
 void launch_batch_sample(lbm_cde* h, hipStream_t s, double* hist) {
-  const int nr = (int)h->runs.size();
-  const int Q = h->runs[0].Q;
+  const int nr = (int)h->runs.size();  // batches are D2Q9
   if (h->runs[0].dbl)
-    hipLaunchKernelGGL(k_batch_xmom_partial<double>, dim3(kBatchRedBlocks, nr), dim3(RED_THREADS), 0, s,
-                       h->dev_runs, Q, h->dev_clock, h->batch_partial);
+    hipLaunchKernelGGL((k_batch_xmom_partial<double, 9>), dim3(kBatchRedBlocks, nr), dim3(RED_THREADS), 0, s,
+                       h->dev_runs, h->dev_clock, h->batch_partial);
   else
-    hipLaunchKernelGGL(k_batch_xmom_partial<float>, dim3(kBatchRedBlocks, nr), dim3(RED_THREADS), 0, s,
-                       h->dev_runs, Q, h->dev_clock, h->batch_partial);
+    hipLaunchKernelGGL((k_batch_xmom_partial<float, 9>), dim3(kBatchRedBlocks, nr), dim3(RED_THREADS), 0, s,
+                       h->dev_runs, h->dev_clock, h->batch_partial);
   hipLaunchKernelGGL(k_batch_xmom_final, dim3(nr), dim3(RED_THREADS), 0, s, h->batch_partial, kBatchRedBlocks, nr,
                      h->dev_clock, hist);
   hipLaunchKernelGGL(k_tick, dim3(1), dim3(64), 0, s, h->dev_clock, 1, 1);
@@ -1892,9 +1894,12 @@ int lbm_cde_moments(lbm_cde_handle h, int32_t run, double* phi_out) {
   if (!r || !phi_out) return fail(h, LBM_CDE_EINVAL, "moments: bad handle, run or pointer");
   const RunArgs a = make_args(h, *r, r->cur);
   const unsigned blocks = (unsigned)((r->nodes + 255) / 256);
-  if (r->dbl) hipLaunchKernelGGL(k_moments<double>, dim3(blocks), dim3(256), 0, h->stream, a, r->Q, phi_out);
-  else if (r->half) hipLaunchKernelGGL(k_moments<__half>, dim3(blocks), dim3(256), 0, h->stream, a, r->Q, phi_out);
-  else hipLaunchKernelGGL(k_moments<float>, dim3(blocks), dim3(256), 0, h->stream, a, r->Q, phi_out);
+  const dim3 g(blocks), b(256);
+  if (r->half) hipLaunchKernelGGL((k_moments<__half, 9>), g, b, 0, h->stream, a, phi_out);
+  else if (r->dbl && r->Q == 9) hipLaunchKernelGGL((k_moments<double, 9>), g, b, 0, h->stream, a, phi_out);
+  else if (r->dbl) hipLaunchKernelGGL((k_moments<double, 15>), g, b, 0, h->stream, a, phi_out);
+  else if (r->Q == 9) hipLaunchKernelGGL((k_moments<float, 9>), g, b, 0, h->stream, a, phi_out);
+  else hipLaunchKernelGGL((k_moments<float, 15>), g, b, 0, h->stream, a, phi_out);
   HIP_TRY(h, hipGetLastError());
   return LBM_CDE_OK;
 }
@@ -1908,11 +1913,15 @@ int lbm_cde_reduce(lbm_cde_handle h, int32_t run, int32_t kind, double x_ref, do
     return fail(h, LBM_CDE_EINVAL, "reduce: x_ref is not finite");
   int rc = reduce_into(h, *r, kind, x_ref, r->red_out);
   if (rc) return rc;
-  double res[4];
-  unsigned long long fl[3] = {0, 0, 0};
-  HIP_TRY(h, hipMemcpyAsync(res, r->red_out, sizeof res, hipMemcpyDeviceToHost, h->stream));
-  HIP_TRY(h, hipMemcpyAsync(fl, r->flags, sizeof fl, hipMemcpyDeviceToHost, h->stream));
+  // the result and the run's flags lie next to each other in the workspace
+  // (layout()): one copy brings both
+  char host[kAlign + 3 * sizeof(unsigned long long)];
+  HIP_TRY(h, hipMemcpyAsync(host, r->red_out, sizeof host, hipMemcpyDeviceToHost, h->stream));
   HIP_TRY(h, hipStreamSynchronize(h->stream));
+  double res[4];
+  unsigned long long fl[3];
+  std::memcpy(res, host, sizeof res);
+  std::memcpy(fl, host + ((const char*)r->flags - (const char*)r->red_out), sizeof fl);
   const unsigned long long over = fl[1], fast = r->uslot ? fl[2] : 0;
   if (kind == LBM_CDE_RED_NONFINITE) {
     out[0] = res[3];
@@ -1942,15 +1951,7 @@ int lbm_cde_reduce_noalloc(lbm_cde_handle h, int32_t run, int32_t kind, double x
                 run, (long long)r->nodes, (long long)(kScratchPartials * kNodesPerPartial));
   const RunArgs a = make_args(h, *r, r->cur);
   double* partial = h->scratch_dev;  // every partial in [0, nb) is written before it is read
-  if (r->dbl)
-    hipLaunchKernelGGL(k_reduce_partial<double>, dim3((unsigned)nb), dim3(RED_THREADS), 0, h->stream, a, r->Q, kind,
-                       x_ref, partial);
-  else if (r->half)
-    hipLaunchKernelGGL(k_reduce_partial<__half>, dim3((unsigned)nb), dim3(RED_THREADS), 0, h->stream, a, r->Q, kind,
-                       x_ref, partial);
-  else
-    hipLaunchKernelGGL(k_reduce_partial<float>, dim3((unsigned)nb), dim3(RED_THREADS), 0, h->stream, a, r->Q, kind,
-                       x_ref, partial);
+  launch_reduce_partial(h, *r, a, kind, x_ref, (unsigned)nb, partial);
   hipLaunchKernelGGL(k_reduce_final, dim3(1), dim3(RED_THREADS), 0, h->stream, (const double*)partial, (int)nb, out);
   HIP_TRY(h, hipGetLastError());
   return LBM_CDE_OK;
