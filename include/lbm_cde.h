@@ -277,9 +277,15 @@ int lbm_cde_set_velocity(lbm_cde_handle h, int32_t run, const double* u);
  * intermediate steps of a tile and its halo in LDS (Eq. 5: a population
  * moves one node per step), so the state crosses HBM once per launch; the
  * steps left over when a call's count is not a multiple go one per launch.
+ * Zero rows per thread name the launches whose waves (64 x 1) march along y
+ * with the steps between in registers, 4 to 6 at a time: for such runs with a
+ * constant D and a constant or separable velocity (factor 1 in z) at least 64
+ * nodes wide, periodic in y with at least 10 rows or bounded by walls; a
+ * call's steps are divided evenly over launches of at most that many.
  * A run that can take several steps per launch starts with 4 (64 x 24
  * tiles in FP32 where the grid allows them, else 64 x 16; 64 x 8 in FP64),
- * any other with one.  A batched handle has
+ * one of 300,000 nodes or more that can march, and a batch of as many, with a
+ * marching launch of 4 to 6; any other with one.  A batched handle has
  * one variant for all its runs; the run index only has to be valid.  Results
  * are bitwise the same for every variant. */
 

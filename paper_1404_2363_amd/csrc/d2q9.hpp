@@ -431,8 +431,8 @@ LBM_FORCEINLINE void tile_rows_d2q9(const RunArgs& a, int64_t tile_x, int64_t ti
 
 // One step of every active run of a batch, in one persistent launch: the
 // grid walks a flat list of BX-wide row tiles spanning all runs.  The
-// global step t is read from device memory (so a captured graph stays valid)
-// and fixes the buffer parity.  The tile list holds the runs in order[] of
+// global step t is read from device memory, toff steps ahead of the clock (so
+// a captured graph stays valid), and fixes the buffer parity.  The tile list holds the runs in order[] of
 // decreasing step budget (unlimited first), so the runs still active at t
 // (budget max_steps > t) own a prefix of it: blocks past that prefix exit at
 // once instead of searching and skipping the tiles of finished runs.
@@ -440,8 +440,8 @@ template <typename R, int BX, bool NT>
 __global__ __launch_bounds__(BX) void k_batch_d2q9(const RunArgs* __restrict__ runs,
                                                    const int64_t* __restrict__ tile_start,
                                                    const int32_t* __restrict__ order, int nruns,
-                                                   const int64_t* __restrict__ clock) {
-  const int64_t t_global = clock[0];
+                                                   const int64_t* __restrict__ clock, int64_t toff) {
+  const int64_t t_global = clock[0] + toff;
   // number of active runs: the first position in order[] whose run is done
   int na;
   {
@@ -523,8 +523,8 @@ LBM_FORCEINLINE void row_source_b(int32_t bc_y, int32_t y, int32_t ny, int& pop,
 template <typename R, int BX, bool NT>
 __global__ __launch_bounds__(BX) void k_batch_rows_d2q9(const BatchRun* __restrict__ runs,
                                                         const uint32_t* __restrict__ tile_start, int nruns,
-                                                        const int64_t* __restrict__ clock) {
-  const int64_t t_global = clock[0];
+                                                        const int64_t* __restrict__ clock, int64_t toff) {
+  const int64_t t_global = clock[0] + toff;
   // active runs: a prefix of the list (runs are stored by decreasing budget)
   int na;
   {

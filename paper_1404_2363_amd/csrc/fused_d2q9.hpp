@@ -383,41 +383,50 @@ LBM_FORCEINLINE RunArgs batch_run_args(const BatchRun& br, int par) {
   return a;
 }
 
-// T steps of every active run of a batch (runs periodic in x, walls or not
-// in y, constant or separable velocity) in one launch: block b takes tile b
-// of a flat list of BX x (BY * NY) tiles over the runs (in order of
-// decreasing budget; blocks past the active runs' tiles exit, and the host
-// launches this kernel only while no run's budget ends inside the launch).
-// The buffer parity is clock[2], which every launch of a batched kernel
-// flips (the one-step kernel's parity, t & 1, equals it between launches of
-// this kernel taken in pairs).
-template <typename R, int BX, int BY, int NY, int T, int UK, bool WY>
-__global__ __launch_bounds__(BX * BY) void k_batch_fused_d2q9(const BatchRun* __restrict__ runs,
-                                                             const uint32_t* __restrict__ tile_start, int nruns,
-                                                             const int64_t* __restrict__ clock) {
-  const uint32_t t = blockIdx.x;
-  // active runs: a prefix of the list (runs are stored by decreasing budget)
-  const int64_t t_global = clock[0];
-  int na;
-  {
-    int l = 0, h = nruns;
-    while (l < h) {
-      const int mid = (l + h) / 2;
-      const int64_t ms = runs[mid].max_steps;
-      if (ms >= 0 && t_global >= ms) h = mid;
-      else l = mid + 1;
-    }
-    na = l;
+// Runs still active at step t: a prefix of the list (stored by decreasing budget).
+LBM_FORCEINLINE int batch_active_runs(const BatchRun* runs, int nruns, int64_t t) {
+  int l = 0, h = nruns;
+  while (l < h) {
+    const int mid = (l + h) / 2;
+    const int64_t ms = runs[mid].max_steps;
+    if (ms >= 0 && t >= ms) h = mid;
+    else l = mid + 1;
   }
-  if (na == 0 || t >= tile_start[na]) return;
+  return l;
+}
+
+// The run (of the first na) whose tiles hold tile t of the flat list.
+LBM_FORCEINLINE int batch_run_of(const uint32_t* tile_start, int na, uint32_t t) {
   int lo = 0, hi = na - 1;
   while (lo < hi) {
     const int mid = (lo + hi + 1) / 2;
     if (tile_start[mid] <= t) lo = mid;
     else hi = mid - 1;
   }
+  return lo;
+}
+
+// T steps of every active run of a batch (runs periodic in x, walls or not
+// in y, constant or separable velocity) in one launch: block b takes tile b
+// of a flat list of BX x (BY * NY) tiles over the runs (in order of
+// decreasing budget; blocks past the active runs' tiles exit, and the host
+// launches this kernel only while no run's budget ends inside the launch).
+// clock[0] + toff is the step before the launch (the clock is advanced once
+// for all the launches of a captured block), clock[2] ^ flip the buffer it
+// reads: every launch of a batched kernel flips the buffer (the one-step
+// kernel's parity, t & 1, equals it between launches of this kernel taken in
+// pairs).
+template <typename R, int BX, int BY, int NY, int T, int UK, bool WY>
+__global__ __launch_bounds__(BX * BY) void k_batch_fused_d2q9(const BatchRun* __restrict__ runs,
+                                                             const uint32_t* __restrict__ tile_start, int nruns,
+                                                             const int64_t* __restrict__ clock, int64_t toff,
+                                                             int flip) {
+  const uint32_t t = blockIdx.x;
+  const int na = batch_active_runs(runs, nruns, clock[0] + toff);
+  if (na == 0 || t >= tile_start[na]) return;
+  const int lo = batch_run_of(tile_start, na, t);
   const BatchRun& br = runs[lo];
-  const RunArgs a = batch_run_args<R>(br, (int)(clock[2] & 1));
+  const RunArgs a = batch_run_args<R>(br, (int)(clock[2] & 1) ^ flip);
   const uint32_t ntx = (br.nx + BX - 1) / BX, local = t - tile_start[lo];
   const uint32_t tyi = local / ntx;
   fused_tile<R, BX, BY, NY, T, UK, WY>(a, local - tyi * ntx, tyi);

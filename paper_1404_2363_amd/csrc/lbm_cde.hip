@@ -31,6 +31,7 @@
 #include "fused_d2q9.hpp"
 #include "adjoint_fused_d2q9.hpp"
 #include "stability.hpp"
+#include "strip_d2q9.hpp"
 
 using namespace lbm;
 
@@ -48,6 +49,7 @@ thread_local std::string g_init_error;
 
 constexpr size_t kAlign = 256;
 constexpr int kGraphSteps = 32;   // steps per captured graph (an even number)
+constexpr int kGraphStrip = 48;   // ... of marching launches: eight of six steps, none shorter
 constexpr size_t kMaxAdjGraphs = 16;  // captured adjoint-segment parts kept per handle
 constexpr int kBatchRedBlocks = 64;  // reduction blocks per run in batched sampling
 
@@ -64,7 +66,8 @@ size_t plane_skew() {
 
 // A launch variant of the step kernel: tile shape, store kind, block order,
 // for the batched persistent launch its number of blocks, and the number of
-// steps one launch takes (more than one: the LDS-blocked D2Q9 kernel).
+// steps one launch takes (more than one: the LDS-blocked D2Q9 kernel, or with
+// ny = 0 the marching one).
 struct Variant {
   int bx, by, ny;
   bool nt;       // non-temporal (streaming) stores
@@ -75,7 +78,11 @@ struct Variant {
     return bx == o.bx && by == o.by && ny == o.ny && nt == o.nt && xcd == o.xcd && grid == o.grid &&
            fuse == o.fuse;
   }
+  bool strip() const { return ny == 0; }  // waves marching along y (strip_d2q9.hpp)
 };
+
+// The marching launch of T steps.
+Variant strip_variant(int T) { return Variant{64, 1, 0, false, 1, 0, T}; }
 
 struct Run {
   lbm_cde_run_desc d;
@@ -145,8 +152,10 @@ struct lbm_cde {
   // several steps per launch for the whole batch (fuse > 1), used for every
   // kGraphSteps block in which no run's budget ends; batch_var steps the rest
   Variant batch_fuse{64, 8, 2, true, 0, 0, 1};
-  uint32_t* dev_tiles_f = nullptr;     // tile starts of the multi-step launch, batch order
-  std::vector<int64_t> batch_prefix_f; // host copy
+  uint32_t* dev_tiles_f = nullptr;     // tile starts of the multi-step launch, batch order (the
+                                       // marching one has a list for each number of steps)
+  std::vector<int64_t> batch_prefix_f[kStripMax - 1];  // host copies
+  int32_t strip_rows[kStripMax - 1] = {};              // rows of a chunk of the marching launches
   std::map<unsigned, hipGraphExec_t> batch_fgraphs;
   std::map<uint64_t, hipGraphExec_t> sample_fgraphs;
   int64_t sample_every = 0;
@@ -518,7 +527,8 @@ size_t layout(Run& r, char* base) {
 
 // Number of tile rows of a launch (y tiles times z planes).
 int64_t tile_rows(const Run& r, const Variant& v) {
-  return (r.d.ny + (int64_t)v.by * v.ny - 1) / ((int64_t)v.by * v.ny) * r.d.nz;
+  const int64_t th = v.strip() ? 1 : (int64_t)v.by * v.ny;
+  return (r.d.ny + th - 1) / th * r.d.nz;
 }
 
 // Bytes of one state: the population planes (and, split storage, phi).
@@ -582,7 +592,7 @@ RunArgs make_args(const lbm_cde* h, const Run& r, int parity, const Variant* lau
   // tile counts of the launch's block shape (16-bit runs: the split kernels
   // tile BX x BY nodes; the literal kernel 256 x 1)
   const int64_t tbx = r.half && !r.split ? 256 : var.bx;
-  const int64_t tby = r.half && !r.split ? 1 : (int64_t)var.by * (r.half ? 1 : var.ny);
+  const int64_t tby = (r.half && !r.split) || var.strip() ? 1 : (int64_t)var.by * (r.half ? 1 : var.ny);
   a.tiles_x = make_fastdiv((uint32_t)((r.d.nx + tbx - 1) / tbx));
   a.tiles_y = make_fastdiv((uint32_t)((r.d.ny + tby - 1) / tby));
   a.rows32 = r.d.lattice == LBM_CDE_D2Q9 && !r.half && r.d.bc[0] == LBM_CDE_PERIODIC && !r.node_par &&
@@ -608,7 +618,7 @@ size_t batch_bytes(int32_t nruns) {
   return align_up(sizeof(RunArgs) * nruns) + align_up(sizeof(int64_t) * (nruns + 1)) +
          align_up(sizeof(int32_t) * nruns) + align_up(3 * sizeof(int64_t)) +
          align_up(sizeof(double) * 3 * kBatchRedBlocks * nruns) + align_up(sizeof(BatchRun) * nruns) +
-         2 * align_up(sizeof(uint32_t) * (nruns + 1));
+         kStripMax * align_up(sizeof(uint32_t) * (nruns + 1));
 }
 
 // ---- kernel dispatch ------------------------------------------------------
@@ -787,8 +797,50 @@ bool fused_ok(const Run& r, const Variant& v) {
          v.grid == 0;
 }
 
+// The marching launch takes the runs of the tile kernel with a constant D, a
+// constant or separable velocity (unit z factors), at least a wave's columns
+// in x and, periodic in y, the rows that its halo wraps over.
+bool strip_ok(const Run& r, int T) {
+  const bool wy = r.d.bc[1] != LBM_CDE_PERIODIC;
+  return T >= 2 && T <= kStripMax && r.d.lattice == LBM_CDE_D2Q9 && !r.half && r.d.nz == 1 &&
+         r.d.bc[0] == LBM_CDE_PERIODIC && (r.d.model == LBM_CDE_MRT_A || r.d.model == LBM_CDE_MRT_B3) &&
+         r.d.u_kind != LBM_CDE_U_FIELD && (r.d.u_kind == LBM_CDE_U_CONST || r.u_z_unit) && !r.node_par &&
+         r.d.nx >= 64 && (wy || r.d.ny >= 2 * (kStripMax - 1)) && (double)r.nodes * (double)r.elem < 4294967296.0 &&
+         r.d.nx < (1ll << 24) && r.d.ny < (1ll << 24);
+}
+
+template <bool DBL, int T>
+void launch_strip(const RunArgs a, hipStream_t s) {
+  if (DBL) launch_strip_f64(T, a, s);
+  else launch_strip_f32(T, a, s);
+}
+const StepFn kStrip[2][kStripMax - 1] = {{launch_strip<false, 2>, launch_strip<false, 3>, launch_strip<false, 4>,
+                                          launch_strip<false, 5>, launch_strip<false, 6>},
+                                         {launch_strip<true, 2>, launch_strip<true, 3>, launch_strip<true, 4>,
+                                          launch_strip<true, 5>, launch_strip<true, 6>}};
+
+// The marching launch that a run starts with (fuse 1: none): large grids whose
+// width fills the strips.  Below about 300,000 nodes the waves of a launch
+// have few rows each and the halo rows dominate (512^2: 17.3 us for six steps
+// in FP32 against 15.6 us for eight in LDS tiles; at 724^2 the tile kernel
+// takes 3.9 us a step, the march 3.8, in FP64 7.8 against 4.8); a strip that
+// keeps less than 70 % of its lanes costs more than the tiles' halo.
+constexpr int64_t kStripNodes = 300000;
+
+Variant strip_start(const Run& r) {
+  StripCut best{1, 0, 1e300};
+  for (int T = 4; T <= kStripMax; ++T) {
+    const int64_t nsx = (r.d.nx + strip_width(T) - 1) / strip_width(T);
+    if (!strip_ok(r, T) || r.nodes < kStripNodes || 10 * r.d.nx < 7 * 64 * nsx) continue;
+    const StripCut c = strip_cut_run(T, r.d.nx, r.d.ny, r.dbl);
+    if (c.cost < best.cost) best = c;
+  }
+  return strip_variant(best.T);
+}
+
 StepFn find_step(const Run& r, const Variant& v) {
   const int p = r.dbl ? 1 : 0, w = r.walls ? 1 : 0;
+  if (v.strip()) return strip_ok(r, v.fuse) && v == strip_variant(v.fuse) ? kStrip[p][v.fuse - 2] : nullptr;
   if (v.fuse != 1) {
     if (v.fuse < 2 || !v.nt || !fused_ok(r, v)) return nullptr;
     for (const auto& e : kFused)
@@ -820,6 +872,17 @@ void launch_variant(lbm_cde* h, Run& r, const Variant& v, hipStream_t s) {
   r.steps += v.fuse;
 }
 
+// n steps as marching launches of at most T steps, as equal as they can be
+// (a launch costs nearly the same whatever it takes).  parity 0 or 1: an even
+// or odd number of launches where that is possible; -1: either.
+std::vector<int> strip_split(int64_t n, int T, int parity) {
+  int64_t k = (n + T - 1) / T;
+  if (parity >= 0 && (k & 1) != parity && k < n) ++k;
+  std::vector<int> out;
+  for (int64_t i = 0; i < k; ++i) out.push_back((int)(n / k + (i < n % k ? 1 : 0)));
+  return out;
+}
+
 // Enqueue n steps of run r (fewer where its budget ends first): launches of
 // its variant while they fit, one-step launches for the rest.  With `even`,
 // one multi-step launch is traded for one-step launches where that makes the
@@ -828,6 +891,11 @@ void launch_variant(lbm_cde* h, Run& r, const Variant& v, hipStream_t s) {
 int64_t enqueue_run(lbm_cde* h, Run& r, int64_t n, hipStream_t s, bool even = false) {
   if (r.d.max_steps >= 0) n = std::min<int64_t>(n, std::max<int64_t>(r.d.max_steps - r.steps, 0));
   const int T = r.var.fuse;
+  if (r.var.strip()) {
+    const std::vector<int> parts = strip_split(n, T, even ? 0 : -1);
+    for (int t : parts) launch_variant(h, r, t > 1 ? strip_variant(t) : r.var1, s);
+    return (int64_t)parts.size();
+  }
   int64_t q = T > 1 ? n / T : 0, rest = n - q * T;
   if (even && T > 1 && q > 0 && ((q + rest) & 1)) {
     q -= 1;
@@ -837,6 +905,13 @@ int64_t enqueue_run(lbm_cde* h, Run& r, int64_t n, hipStream_t s, bool even = fa
   const Variant& v1 = T > 1 ? r.var1 : r.var;
   for (int64_t k = 0; k < rest; ++k) launch_variant(h, r, v1, s);
   return q + rest;
+}
+
+// Steps of a captured graph of a handle whose runs step on their own.
+int graph_steps(const lbm_cde* h) {
+  for (const auto& r : h->runs)
+    if (!r.var.strip()) return kGraphSteps;
+  return kGraphStrip;
 }
 
 int launch_steps(lbm_cde* h, hipStream_t s, int64_t n) {
@@ -862,8 +937,8 @@ void drop_graphs(lbm_cde* h) {
   h->adj_graphs.clear();
 }
 
-// Capture kGraphSteps steps of every run, each starting from buffer p, on
-// the private stream.  Callers make sure that every run has kGraphSteps
+// Capture graph_steps() steps of every run, each starting from buffer p, on
+// the private stream.  Callers make sure that every run has that many
 // steps of budget left.  A run whose steps take an odd number of launches
 // would end in the other buffer: then no graph is kept (graph_off) and the
 // steps are launched one call at a time.
@@ -875,7 +950,7 @@ int build_graph(lbm_cde* h, int p) {
   }
   bool even = true;
   HIP_TRY(h, hipStreamBeginCapture(h->capture, hipStreamCaptureModeThreadLocal));
-  for (auto& r : h->runs) even = (enqueue_run(h, r, kGraphSteps, h->capture, true) % 2 == 0) && even;
+  for (auto& r : h->runs) even = (enqueue_run(h, r, graph_steps(h), h->capture, true) % 2 == 0) && even;
   hipGraph_t g = nullptr;
   hipError_t e = hipStreamEndCapture(h->capture, &g);
   for (size_t i = 0; i < h->runs.size(); ++i) std::tie(h->runs[i].steps, h->runs[i].cur) = saved[i];
@@ -996,20 +1071,21 @@ int choose_fp16_scale(Run& r, lbm_cde* h, const double* phi0, hipStream_t s) {
 }
 
 // Batched launch variants (row-tile width, streaming stores) compiled into the library.
-using BatchFn = void (*)(const lbm_cde*, hipStream_t, unsigned);
+// (handle, stream, grid, steps since the device clock, launches since it & 1)
+using BatchFn = void (*)(const lbm_cde*, hipStream_t, unsigned, int64_t, int);
 struct BatchEntry {
   int bx;
   bool nt;
   BatchFn fn[2];  // [double?]
 };
 template <typename R, int BX, bool NT>
-void launch_batch(const lbm_cde* h, hipStream_t s, unsigned grid) {
+void launch_batch(const lbm_cde* h, hipStream_t s, unsigned grid, int64_t toff, int) {
   if (h->batch_lean)
     hipLaunchKernelGGL((k_batch_rows_d2q9<R, BX, NT>), dim3(grid), dim3(BX), 0, s, h->dev_brun, h->dev_tiles32,
-                       (int)h->runs.size(), h->dev_clock);
+                       (int)h->runs.size(), h->dev_clock, toff);
   else
     hipLaunchKernelGGL((k_batch_d2q9<R, BX, NT>), dim3(grid), dim3(BX), 0, s, h->dev_runs, h->dev_tiles,
-                       h->dev_order, (int)h->runs.size(), h->dev_clock);
+                       h->dev_order, (int)h->runs.size(), h->dev_clock, toff);
 }
 #define BATCH_ENTRY(BX, NT) \
   BatchEntry { BX, NT, {launch_batch<float, BX, NT>, launch_batch<double, BX, NT>} }
@@ -1127,25 +1203,40 @@ int apply_batch_variant(lbm_cde* h, const Variant& v, std::vector<int64_t>* tile
 // block of multi-step launches leaves the state in the buffer that the
 // step count's parity names.
 template <typename R, int BX, int BY, int NY, int T>
-void launch_batch_fused(const lbm_cde* h, hipStream_t s, unsigned grid) {
+void launch_batch_fused(const lbm_cde* h, hipStream_t s, unsigned grid, int64_t toff, int flip) {
   const Run& r0 = h->runs[0];
   const int nr = (int)h->runs.size();
   const dim3 g(grid), b(BX, BY);
+  const bool uc = r0.d.u_kind == LBM_CDE_U_CONST;
+#define LBM_BATCH_FUSED(UK, WY)                                                                                       \
+  hipLaunchKernelGGL((k_batch_fused_d2q9<R, BX, BY, NY, T, UK, WY>), g, b, 0, s, h->dev_brun, h->dev_tiles_f, nr, \
+                     h->dev_clock, toff, flip)
   if (r0.d.bc[1] != LBM_CDE_PERIODIC) {
-    if (r0.d.u_kind == LBM_CDE_U_CONST)
-      hipLaunchKernelGGL((k_batch_fused_d2q9<R, BX, BY, NY, T, 0, true>), g, b, 0, s, h->dev_brun, h->dev_tiles_f,
-                         nr, h->dev_clock);
-    else
-      hipLaunchKernelGGL((k_batch_fused_d2q9<R, BX, BY, NY, T, 1, true>), g, b, 0, s, h->dev_brun, h->dev_tiles_f,
-                         nr, h->dev_clock);
-  } else if (r0.d.u_kind == LBM_CDE_U_CONST) {
-    hipLaunchKernelGGL((k_batch_fused_d2q9<R, BX, BY, NY, T, 0, false>), g, b, 0, s, h->dev_brun, h->dev_tiles_f, nr,
-                       h->dev_clock);
+    if (uc) LBM_BATCH_FUSED(0, true);
+    else LBM_BATCH_FUSED(1, true);
+  } else if (uc) {
+    LBM_BATCH_FUSED(0, false);
   } else {
-    hipLaunchKernelGGL((k_batch_fused_d2q9<R, BX, BY, NY, T, 1, false>), g, b, 0, s, h->dev_brun, h->dev_tiles_f, nr,
-                       h->dev_clock);
+    LBM_BATCH_FUSED(1, false);
   }
+#undef LBM_BATCH_FUSED
 }
+
+template <bool DBL, int T>
+void launch_batch_strip(const lbm_cde* h, hipStream_t s, unsigned grid, int64_t toff, int flip) {
+  const Run& r0 = h->runs[0];
+  const int nr = (int)h->runs.size();
+  const StripBatch v{h->dev_brun, h->dev_tiles_f + (T - 2) * (align_up(sizeof(uint32_t) * (nr + 1)) / sizeof(uint32_t)),
+                     nr, h->dev_clock, toff, flip, h->strip_rows[T - 2], r0.d.u_kind == LBM_CDE_U_CONST,
+                     r0.d.bc[1] != LBM_CDE_PERIODIC, (grid + 63u) / 64u * 64u};
+  if (DBL) launch_strip_batch_f64(T, v, s);
+  else launch_strip_batch_f32(T, v, s);
+}
+const BatchFn kBatchStrip[2][kStripMax - 1] = {
+    {launch_batch_strip<false, 2>, launch_batch_strip<false, 3>, launch_batch_strip<false, 4>,
+     launch_batch_strip<false, 5>, launch_batch_strip<false, 6>},
+    {launch_batch_strip<true, 2>, launch_batch_strip<true, 3>, launch_batch_strip<true, 4>,
+     launch_batch_strip<true, 5>, launch_batch_strip<true, 6>}};
 
 template <typename R, int BX, int BY, int NY, int T>
 constexpr BatchFn batch_fused_fn() {
@@ -1170,14 +1261,17 @@ const BatchFusedEntry kBatchFused[] = {BATCH_FUSED_ENTRY(64, 8, 2, 4), BATCH_FUS
 // The multi-step batched launch of variant v, or null where it is not built
 // or some run does not allow it.
 BatchFn find_batch_fused(const lbm_cde* h, const Variant& v) {
-  if (!h->batch_lean || v.fuse < 2 || (kGraphSteps / v.fuse) % 2 != 0 || kGraphSteps % v.fuse != 0 || !v.nt ||
-      v.xcd != 0 || v.grid != 0 || h->runs.empty())
+  if (!h->batch_lean || v.fuse < 2 || h->runs.empty()) return nullptr;
+  const bool strip = v == strip_variant(v.fuse);
+  if (!strip && ((kGraphSteps / v.fuse) % 2 != 0 || kGraphSteps % v.fuse != 0 || !v.nt || v.xcd != 0 || v.grid != 0))
     return nullptr;
   const Run& r0 = h->runs[0];
   for (const Run& r : h->runs)
-    if (!fused_ok(r, v) || r.node_par || r.d.u_kind == LBM_CDE_U_FIELD || r.d.u_kind != r0.d.u_kind ||
-        (r.d.bc[1] == LBM_CDE_PERIODIC) != (r0.d.bc[1] == LBM_CDE_PERIODIC) || r.dbl != r0.dbl)
+    if (!(strip ? strip_ok(r, v.fuse) : fused_ok(r, v)) || r.node_par || r.d.u_kind == LBM_CDE_U_FIELD ||
+        r.d.u_kind != r0.d.u_kind || (r.d.bc[1] == LBM_CDE_PERIODIC) != (r0.d.bc[1] == LBM_CDE_PERIODIC) ||
+        r.dbl != r0.dbl)
       return nullptr;
+  if (strip) return kBatchStrip[r0.dbl ? 1 : 0][v.fuse - 2];
   for (const auto& e : kBatchFused)
     if (e.bx == v.bx && e.by == v.by && e.ny == v.ny && e.T == v.fuse) return e.fn[r0.dbl ? 1 : 0];
   return nullptr;
@@ -1189,44 +1283,89 @@ std::vector<Variant> batch_fused_candidates(const lbm_cde* h) {
     const Variant c{e.bx, e.by, e.ny, true, 0, 0, e.T};
     if (find_batch_fused(h, c)) out.push_back(c);
   }
+  // the marching launches where they can win: smaller batches leave most SIMDs
+  // without a wave (set_variant takes them there as well)
+  int64_t nodes = 0;
+  for (const Run& r : h->runs) nodes += r.nodes;
+  for (int T = 4; T <= kStripMax && nodes >= 100000; ++T)
+    if (find_batch_fused(h, strip_variant(T))) out.push_back(strip_variant(T));
   return out;
+}
+
+// The cut of a batch at T steps per marching launch.
+StripCut strip_cut_batch(const lbm_cde* h, int T) {
+  int64_t tall = 1;
+  for (const Run& r : h->runs) tall = std::max<int64_t>(tall, r.d.ny);
+  return strip_cut(T, tall, h->runs[0].dbl, [&](auto f) {
+    for (const Run& r : h->runs) f(r.d.ny, (r.d.nx + strip_width(T) - 1) / strip_width(T));
+  });
+}
+
+// The marching launch that a batch starts with (fuse 1: none; see strip_start).
+Variant batch_strip_start(const lbm_cde* h) {
+  int64_t nodes = 0;
+  for (const Run& r : h->runs) nodes += r.nodes;
+  StripCut best{1, 0, 1e300};
+  for (int T = 4; T <= kStripMax; ++T) {
+    int64_t lanes = 0, kept = 0;
+    for (const Run& r : h->runs) {
+      lanes += (r.d.nx + strip_width(T) - 1) / strip_width(T) * 64;
+      kept += r.d.nx;
+    }
+    if (nodes < kStripNodes || 10 * kept < 7 * lanes || !find_batch_fused(h, strip_variant(T))) continue;
+    const StripCut c = strip_cut_batch(h, T);
+    if (c.cost < best.cost) best = c;
+  }
+  return strip_variant(best.T);
 }
 
 // Make v the multi-step batched launch (v.fuse > 1; validated by the caller
 // with find_batch_fused) or switch it off (v.fuse == 1): the flat list of
-// BX x (BY * NY) tiles over the runs, in batch order, goes to the workspace.
+// BX x (BY * NY) tiles over the runs, in batch order, goes to the workspace,
+// or the lists of units of the marching launches of 2 .. kStripMax steps.
 int apply_batch_fused(lbm_cde* h, const Variant& v) {
-  if (v.fuse > 1) {
-    const int32_t nruns = (int32_t)h->runs.size();
+  const int32_t nruns = (int32_t)h->runs.size();
+  const size_t list = align_up(sizeof(uint32_t) * (nruns + 1));
+  for (int j = 0; v.fuse > 1 && j < (v.strip() ? kStripMax - 1 : 1); ++j) {
+    int64_t tw = v.bx, th = (int64_t)v.by * v.ny;
+    if (v.strip()) {
+      tw = strip_width(j + 2);
+      th = h->strip_rows[j] = strip_cut_batch(h, j + 2).L;
+    }
     std::vector<int64_t> tiles(1, 0);
-    const int64_t th = (int64_t)v.by * v.ny;
     for (int32_t k = 0; k < nruns; ++k) {
       const Run& r = h->runs[h->batch_order[k]];
-      tiles.push_back(tiles.back() + (r.d.nx + v.bx - 1) / v.bx * ((r.d.ny + th - 1) / th));
+      tiles.push_back(tiles.back() + (r.d.nx + tw - 1) / tw * ((r.d.ny + th - 1) / th));
     }
     if (tiles.back() >= ((int64_t)1 << 31)) return fail(h, LBM_CDE_EINVAL, "batch: too many tiles");
     std::vector<uint32_t> t32(nruns + 1);
     for (int32_t k = 0; k <= nruns; ++k) t32[k] = (uint32_t)tiles[k];
-    HIP_TRY(h, hipMemcpyAsync(h->dev_tiles_f, t32.data(), sizeof(uint32_t) * (nruns + 1), hipMemcpyHostToDevice,
-                              h->stream));
+    HIP_TRY(h, hipMemcpyAsync((char*)h->dev_tiles_f + j * list, t32.data(), sizeof(uint32_t) * (nruns + 1),
+                              hipMemcpyHostToDevice, h->stream));
     HIP_TRY(h, hipStreamSynchronize(h->stream));
-    h->batch_prefix_f = tiles;
+    h->batch_prefix_f[j] = tiles;
   }
   drop_graphs(h);
   h->batch_fuse = v;
   return LBM_CDE_OK;
 }
 
-// Launch grid of the multi-step batched launch from step t on: the tiles of
+// The tile list that a multi-step launch of the batch goes by.
+const std::vector<int64_t>& batch_tiles_of(const lbm_cde* h, const Variant& v) {
+  return h->batch_prefix_f[v.strip() ? v.fuse - 2 : 0];
+}
+
+// Launch grid of the multi-step batched launch v from step t on: the tiles of
 // the runs still active, rounded up to a power of two (blocks past them exit).
-unsigned batch_fgrid_at(const lbm_cde* h, int64_t t) {
+unsigned batch_fgrid_at(const lbm_cde* h, int64_t t, const Variant& v) {
+  const std::vector<int64_t>& prefix = batch_tiles_of(h, v);
   int64_t active = 0;
   for (size_t k = 0; k < h->batch_order.size(); ++k) {
     const int64_t ms = h->runs[h->batch_order[k]].d.max_steps;
     if (ms >= 0 && t >= ms) break;
-    active = h->batch_prefix_f[k + 1];
+    active = prefix[k + 1];
   }
-  const int64_t total = h->batch_prefix_f.back();
+  const int64_t total = prefix.back();
   int64_t g = 64;
   while (g < active && g < total) g *= 2;
   return (unsigned)std::max<int64_t>(1, std::min(g, total));
@@ -1235,7 +1374,7 @@ unsigned batch_fgrid_at(const lbm_cde* h, int64_t t) {
 // Whether steps t .. t + n of a batch may take the multi-step launch: it is
 // on, and no run's budget ends strictly inside the span.
 bool batch_fused_span(const lbm_cde* h, int64_t t, int64_t n) {
-  if (h->batch_fuse.fuse < 2 || n < 2 * h->batch_fuse.fuse) return false;
+  if (h->batch_fuse.fuse < 2 || n < (h->batch_fuse.strip() ? 3 : 2 * h->batch_fuse.fuse)) return false;
   for (const Run& r : h->runs) {
     const int64_t ms = r.d.max_steps;
     if (ms >= 0 && ms > t && ms < t + n) return false;
@@ -1261,13 +1400,19 @@ int init_runs(lbm_cde* h, const lbm_cde_run_desc* runs, int32_t nruns, const dou
     r.walls = false;
     for (int a = 0; a < r.dim; ++a) r.walls |= r.d.bc[a] != LBM_CDE_PERIODIC;
     r.var = default_variant(r.d.lattice, r.d.precision);
+    if (r.d.u_kind == LBM_CDE_U_SEPARABLE && r.dim == 2) {
+      const size_t st = 1 + r.d.nx + r.d.ny + r.d.nz;
+      r.u_z_unit = r.d.u_tables[st - 1] == 1.0 && r.d.u_tables[2 * st - 1] == 1.0;
+    }
     {
-      // runs that can take several steps per launch do so by default (64 x 24
-      // tiles, 4 steps, XCD-contiguous order in FP32, else 64 x 16; 64 x 8,
+      // runs that can take several steps per launch do so by default: large
+      // ones six by the marching kernel, the others four (64 x 24 tiles, 4 steps, XCD-contiguous order in FP32, else 64 x 16; 64 x 8,
       // 4 steps, XCD-contiguous order in FP64)
       const Variant multi = r.dbl ? Variant{64, 4, 2, true, 1, 0, 4} : Variant{64, 12, 2, true, 1, 0, 4};
       const Variant multi16 = Variant{64, 8, 2, true, 0, 0, 4};
-      if (r.d.lattice == LBM_CDE_D2Q9 && !r.half && find_step(r, multi)) r.var = multi;
+      const Variant march = strip_start(r);
+      if (march.fuse > 1) r.var = march;
+      else if (r.d.lattice == LBM_CDE_D2Q9 && !r.half && find_step(r, multi)) r.var = multi;
       else if (r.d.lattice == LBM_CDE_D2Q9 && !r.half && !r.dbl && find_step(r, multi16)) r.var = multi16;
     }
     if (r.split && h->env16_set) r.var = h->env16;
@@ -1284,10 +1429,6 @@ int init_runs(lbm_cde* h, const lbm_cde_run_desc* runs, int32_t nruns, const dou
     hipStream_t s = h->stream;
     if (orig.u_kind == LBM_CDE_U_SEPARABLE) {
       const size_t n = (size_t)r.dim * (1 + orig.nx + orig.ny + orig.nz);
-      if (r.dim == 2) {
-        const size_t st = 1 + orig.nx + orig.ny + orig.nz;
-        r.u_z_unit = orig.u_tables[st - 1] == 1.0 && orig.u_tables[2 * st - 1] == 1.0;
-      }
       if (r.dbl) {
         HIP_TRY(nullptr, hipMemcpyAsync(r.utab, orig.u_tables, n * 8, hipMemcpyHostToDevice, s));
         HIP_TRY(nullptr, hipStreamSynchronize(s));  // the caller's table may go away after init
@@ -1372,14 +1513,17 @@ int init_runs(lbm_cde* h, const lbm_cde_run_desc* runs, int32_t nruns, const dou
     }
     if (std::getenv("LBM_CDE_BATCH_GENERAL")) h->batch_lean = false;  // the general kernel for every batch
     // tile list in order of decreasing step budget (unlimited first), so that
-    // the active runs always own a prefix of it
+    // the active runs always own a prefix of it, and of decreasing height
     std::vector<int32_t> order(nruns);
     for (int32_t i = 0; i < nruns; ++i) order[i] = i;
     auto budget = [&](int32_t i) {
       const int64_t m = h->runs[i].d.max_steps;
       return m < 0 ? INT64_MAX : m;
     };
-    std::stable_sort(order.begin(), order.end(), [&](int32_t x, int32_t y) { return budget(x) > budget(y); });
+    std::stable_sort(order.begin(), order.end(), [&](int32_t x, int32_t y) {
+      if (budget(x) != budget(y)) return budget(x) > budget(y);
+      return h->runs[x].d.ny > h->runs[y].d.ny;  // tall channels first: their waves march the longest
+    });
     h->batch_order = order;
     hipStream_t s = h->stream;
     HIP_TRY(nullptr, hipMemcpyAsync(h->dev_runs, args.data(), sizeof(RunArgs) * nruns, hipMemcpyHostToDevice, s));
@@ -1397,6 +1541,8 @@ int init_runs(lbm_cde* h, const lbm_cde_run_desc* runs, int32_t nruns, const dou
     // "BXxBYxNYxT" fixes the multi-step one
     Variant fv = h->runs[0].dbl ? Variant{64, 4, 2, true, 0, 0, 4} : Variant{64, 12, 2, true, 0, 0, 4};
     if (!find_batch_fused(h, fv)) fv = Variant{64, 8, 2, true, 0, 0, 4};
+    const Variant march = batch_strip_start(h);
+    if (march.fuse > 1) fv = march;
     int fbx, fby, fny, ft;
     if (const char* e = std::getenv("LBM_CDE_BATCH_FUSE"))
       if (std::sscanf(e, "%dx%dx%dx%d", &fbx, &fby, &fny, &ft) == 4) fv = Variant{fbx, fby, fny, true, 0, 0, ft};
@@ -1426,44 +1572,54 @@ unsigned batch_grid_at(const lbm_cde* h, int64_t t) {
   return std::min(g, h->batch_grid);
 }
 
-// One batched step: the persistent kernel, then the clock tick.
-void launch_batch_step(lbm_cde* h, hipStream_t s, unsigned grid) {
-  find_batch(h->batch_var)->fn[h->runs[0].dbl ? 1 : 0](h, s, grid);
-  hipLaunchKernelGGL(k_tick, dim3(1), dim3(64), 0, s, h->dev_clock, 0, 1);
-}
-
-// Sample the x-moments of every run into hist[row], then advance the row clock.
-void launch_batch_sample(lbm_cde* h, hipStream_t s, double* hist) {
+// Sample the x-moments of every run, `toff` steps ahead of the device clock,
+// into the next history row.
+void launch_batch_sample(lbm_cde* h, hipStream_t s, double* hist, int64_t toff) {
   const int nr = (int)h->runs.size();  // batches are D2Q9
   if (h->runs[0].dbl)
     hipLaunchKernelGGL((k_batch_xmom_partial<double, 9>), dim3(kBatchRedBlocks, nr), dim3(RED_THREADS), 0, s,
-                       h->dev_runs, h->dev_clock, h->batch_partial);
+                       h->dev_runs, h->dev_clock, toff, h->batch_partial);
   else
     hipLaunchKernelGGL((k_batch_xmom_partial<float, 9>), dim3(kBatchRedBlocks, nr), dim3(RED_THREADS), 0, s,
-                       h->dev_runs, h->dev_clock, h->batch_partial);
+                       h->dev_runs, h->dev_clock, toff, h->batch_partial);
   hipLaunchKernelGGL(k_batch_xmom_final, dim3(nr), dim3(RED_THREADS), 0, s, h->batch_partial, kBatchRedBlocks, nr,
                      h->dev_clock, hist);
-  hipLaunchKernelGGL(k_tick, dim3(1), dim3(64), 0, s, h->dev_clock, 1, 1);
 }
 
-// Capture `steps` batched steps of the given grid (and, with hist, one
-// sample) as a graph.  With gridf > 0 the steps go in pairs of multi-step
-// launches of that grid as far as they fit, the rest one per launch.
+// Steps of a captured block of a batch.
+int batch_graph_steps(const lbm_cde* h) { return h->batch_fuse.strip() ? kGraphStrip : kGraphSteps; }
+
+// Enqueue `steps` batched steps of the given grid (and, with hist, one
+// sample), then advance the device clock over them.  With gridf > 0 the steps
+// go in multi-step launches of that grid, the rest one per launch: marching
+// ones share all the steps (at least 3), odd in number where the steps are,
+// the others go in pairs, so that afterwards the state lies in the buffer
+// that the step count's parity names.
+void enqueue_batch(lbm_cde* h, hipStream_t s, int64_t steps, double* hist, unsigned grid, unsigned gridf) {
+  int64_t t = 0, launches = 0;
+  const int64_t t0 = h->global_steps;  // the runs active now stay so over the multi-step launches
+  if (gridf > 0) {
+    std::vector<int> parts;
+    if (h->batch_fuse.strip()) parts = strip_split(steps, h->batch_fuse.fuse, (int)(steps & 1));
+    else parts.assign((size_t)(steps / (2 * h->batch_fuse.fuse) * 2), h->batch_fuse.fuse);
+    for (int n : parts) {
+      if (n == 1) break;  // a single step left over: one step per launch, below
+      Variant v = h->batch_fuse;
+      v.fuse = n;
+      find_batch_fused(h, v)(h, s, batch_fgrid_at(h, t0, v), t, (int)(launches++ & 1));
+      t += n;
+    }
+  }
+  const BatchFn one = find_batch(h->batch_var)->fn[h->runs[0].dbl ? 1 : 0];
+  for (; t < steps; ++t) one(h, s, grid, t, (int)(launches++ & 1));
+  if (hist) launch_batch_sample(h, s, hist, steps);
+  hipLaunchKernelGGL(k_tick, dim3(1), dim3(64), 0, s, h->dev_clock, hist ? 1 : 0, steps, (int)(launches & 1));
+}
+
+// enqueue_batch captured as a graph.
 int capture_batch(lbm_cde* h, int64_t steps, double* hist, unsigned grid, hipGraphExec_t* out, unsigned gridf = 0) {
   HIP_TRY(h, hipStreamBeginCapture(h->capture, hipStreamCaptureModeThreadLocal));
-  int64_t one = steps;
-  if (gridf > 0) {
-    const int T = h->batch_fuse.fuse;
-    const int64_t q = steps / (2 * T) * 2;
-    const BatchFn fn = find_batch_fused(h, h->batch_fuse);
-    for (int64_t k = 0; k < q; ++k) {
-      fn(h, h->capture, gridf);
-      hipLaunchKernelGGL(k_tick, dim3(1), dim3(64), 0, h->capture, h->dev_clock, 2, T);
-    }
-    one = steps - q * T;
-  }
-  for (int64_t t = 0; t < one; ++t) launch_batch_step(h, h->capture, grid);
-  if (hist) launch_batch_sample(h, h->capture, hist);
+  enqueue_batch(h, h->capture, steps, hist, grid, gridf);
   hipGraph_t g = nullptr;
   hipError_t e = hipStreamEndCapture(h->capture, &g);
   if (e != hipSuccess) return fail(h, LBM_CDE_EHIP, "graph capture: %s", hipGetErrorString(e));
@@ -1484,29 +1640,34 @@ void advance_host_clock(lbm_cde* h, int64_t n) {
 int batch_step(lbm_cde* h, int64_t n) {
   int64_t done = 0;
   while (done < n) {
-    const unsigned grid = batch_grid_at(h, h->global_steps);
-    if (n - done >= kGraphSteps) {
-      const bool fused = batch_fused_span(h, h->global_steps, kGraphSteps);
-      const unsigned gridf = fused ? batch_fgrid_at(h, h->global_steps) : 0;
+    // a block of captured steps, or what is left of the call; where a run's
+    // budget ends inside it, the steps up to there
+    const int gs = batch_graph_steps(h);
+    const int64_t t = h->global_steps;
+    int64_t blk = std::min<int64_t>(n - done, gs);
+    for (const Run& r : h->runs)
+      if (r.d.max_steps > t) blk = std::min<int64_t>(blk, r.d.max_steps - t);
+    const unsigned grid = batch_grid_at(h, t);
+    const bool fused = batch_fused_span(h, t, blk);
+    const unsigned gridf = fused ? batch_fgrid_at(h, t, h->batch_fuse) : 0;
+    if (blk == gs) {
       auto& graphs = fused ? h->batch_fgraphs : h->batch_graphs;
       const unsigned key = fused ? gridf : grid;
       hipGraphExec_t& g = graphs[key];
       if (!g) {
-        const int rc = capture_batch(h, kGraphSteps, nullptr, grid, &g, gridf);
+        const int rc = capture_batch(h, gs, nullptr, grid, &g, gridf);
         if (rc) {
           graphs.erase(key);
           return rc;
         }
       }
       HIP_TRY(h, hipGraphLaunch(g, h->stream));
-      advance_host_clock(h, kGraphSteps);
-      done += kGraphSteps;
     } else {
-      launch_batch_step(h, h->stream, grid);
+      enqueue_batch(h, h->stream, blk, nullptr, grid, gridf);
       HIP_TRY(h, hipGetLastError());
-      advance_host_clock(h, 1);
-      done += 1;
     }
+    advance_host_clock(h, blk);
+    done += blk;
   }
   return LBM_CDE_OK;
 }
@@ -1585,13 +1746,13 @@ int time_variant(lbm_cde* h, Run& r, const Variant& v, int trials, double* ms) {
 // and writes the other ones, so the state of every run is unchanged.
 int time_batch(lbm_cde* h, int trials, double* ms, const Variant* fused = nullptr) {
   const BatchFn fn = fused ? find_batch_fused(h, *fused) : find_batch(h->batch_var)->fn[h->runs[0].dbl ? 1 : 0];
-  const unsigned grid = fused ? (unsigned)h->batch_prefix_f.back() : h->batch_grid;
+  const unsigned grid = fused ? (unsigned)batch_tiles_of(h, *fused).back() : h->batch_grid;
   hipEvent_t e0, e1;
   HIP_TRY(h, hipEventCreate(&e0));
   HIP_TRY(h, hipEventCreate(&e1));
-  fn(h, h->stream, grid);  // warm-up
+  fn(h, h->stream, grid, 0, 0);  // warm-up
   HIP_TRY(h, hipEventRecord(e0, h->stream));
-  for (int t = 0; t < trials; ++t) fn(h, h->stream, grid);
+  for (int t = 0; t < trials; ++t) fn(h, h->stream, grid, 0, 0);
   HIP_TRY(h, hipEventRecord(e1, h->stream));
   HIP_TRY(h, hipEventSynchronize(e1));
   float elapsed = 0.f;
@@ -1626,6 +1787,9 @@ std::vector<Variant> run_candidates(const Run& r) {
         const Variant c{e.bx, e.by, e.ny, true, xcd, 0, e.T};
         if (find_step(r, c)) add(c);
       }
+      if (xcd == 1)
+        for (int T = 4; T <= kStripMax; ++T)
+          if (strip_ok(r, T)) add(strip_variant(T));
     }
   }
   return out;
@@ -1854,12 +2018,13 @@ int lbm_cde_step(lbm_cde_handle h, int64_t n) {
   if (n < 0) return fail(h, LBM_CDE_EINVAL, "step: negative step count %lld", (long long)n);
   if (h->batched) return batch_step(h, n);
   int64_t done = 0;
+  const int gs = graph_steps(h);
   while (done < n) {
-    // a captured graph is valid while every run takes all kGraphSteps steps
-    bool uniform = n - done >= kGraphSteps;
+    // a captured graph is valid while every run takes all its steps
+    bool uniform = n - done >= gs;
     int parity = -1;
     for (auto& r : h->runs) {
-      if (r.d.max_steps >= 0 && r.steps + kGraphSteps > r.d.max_steps) uniform = false;
+      if (r.d.max_steps >= 0 && r.steps + gs > r.d.max_steps) uniform = false;
       const int p = r.cur;
       if (parity < 0) parity = p;
       else if (parity != p) uniform = false;
@@ -1870,10 +2035,10 @@ int lbm_cde_step(lbm_cde_handle h, int64_t n) {
     }
     if (uniform && parity >= 0 && h->graph[parity]) {
       HIP_TRY(h, hipGraphLaunch(h->graph[parity], h->stream));
-      for (auto& r : h->runs) r.steps += kGraphSteps;
-      done += kGraphSteps;
+      for (auto& r : h->runs) r.steps += gs;
+      done += gs;
     } else {
-      const int64_t chunk = std::min<int64_t>(n - done, kGraphSteps);
+      const int64_t chunk = std::min<int64_t>(n - done, gs);
       const int rc = launch_steps(h, h->stream, chunk);
       if (rc) return rc;
       done += chunk;
@@ -1977,7 +2142,7 @@ int lbm_cde_run_sampled(lbm_cde_handle h, int64_t n, int64_t every, double* hist
     for (int64_t k = 0; k < rows; ++k) {
       const unsigned grid = batch_grid_at(h, h->global_steps);
       const bool fused = batch_fused_span(h, h->global_steps, every);
-      const unsigned gridf = fused ? batch_fgrid_at(h, h->global_steps) : 0;
+      const unsigned gridf = fused ? batch_fgrid_at(h, h->global_steps, h->batch_fuse) : 0;
       hipGraphExec_t* gp;
       if (fused) gp = &h->sample_fgraphs[((uint64_t)gridf << 32) | grid];
       else gp = &h->sample_graphs[grid];
@@ -2136,10 +2301,14 @@ int lbm_cde_tune(lbm_cde_handle h, int32_t trials) {
     double best = 1e300;
     Variant best_v = r.var;
     for (size_t i = 0; i < cands.size(); ++i) {
+      // a captured block: 32 steps with the rest one at a time, or 48 that a
+      // marching variant divides into launches of (nearly) its length
       const int T = cands[i].fuse, left = kGraphSteps % T;
-      const double block = per_step[i] * (kGraphSteps - left) + best1 * left;
-      if (block / kGraphSteps < best) {
-        best = block / kGraphSteps;
+      const double block = cands[i].strip()
+                               ? per_step[i] * T * (double)strip_split(kGraphStrip, T, 0).size() / kGraphStrip
+                               : (per_step[i] * (kGraphSteps - left) + best1 * left) / kGraphSteps;
+      if (block < best) {
+        best = block;
         best_v = cands[i];
       }
     }
@@ -2156,7 +2325,7 @@ int lbm_cde_get_variant(lbm_cde_handle h, int32_t run, int32_t* out) {
   Run* r = get_run(h, run);
   if (!r || !out) return fail(h, LBM_CDE_EINVAL, "get_variant: bad handle, run or pointer");
   if (h->batched) {
-    if (h->batch_fuse.fuse > 1) variant_out(h->batch_fuse, (int)h->batch_prefix_f.back(), out);
+    if (h->batch_fuse.fuse > 1) variant_out(h->batch_fuse, (int)batch_tiles_of(h, h->batch_fuse).back(), out);
     else variant_out(h->batch_var, h->batch_grid, out);
     return LBM_CDE_OK;
   }

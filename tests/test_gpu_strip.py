@@ -1,0 +1,108 @@
+"""The marching multi-step launches (waves along y, state in registers) against
+one-step launches, bitwise, where a tile or a wall rule can go wrong: widths
+around one, two and three strips (54 columns kept of 64), heights from the
+smallest to ragged ones, every wall kind in y, and step counts that divide
+into every launch length (2 to 6 steps) with and without captured graphs.
+"""
+import dataclasses
+
+import numpy as np
+import pytest
+
+from paper_1404_2363_amd import workloads as W
+from state_views import populations
+
+pytestmark = pytest.mark.gpu
+
+SEQ = [2, 3, 4, 5, 6, 7, 1, 13, 48, 100]
+
+
+def _strip(v):
+    return v["rows_per_thread"] == 0
+
+
+def _one_step(s):
+    return next(v for v in s.variants() if v["steps_per_launch"] == 1 and v["block"] == (256, 1)
+                and v["rows_per_thread"] == 1 and v["nt_stores"] and v["block_order"] == 0)
+
+
+def _case(nx, ny, wall, velocity):
+    if wall == "periodic":
+        wl = W.cellular(nx=nx, ny=ny, steps=1, n_hills=3, sigma=6.0)
+    else:
+        one, prof = np.ones(1), np.sin(np.pi * (np.arange(ny) + 0.5) / ny)
+        wl = W.Workload("channel", "d2q9", (nx, ny), ("periodic", wall), 1, W.random_hills(W.rng_for(7), 3, (nx, ny), 6.0),
+                        D=0.08 * np.eye(2), u_sep=W.SeparableU(np.array([0.05, 0.0]), [
+                            [np.ones(nx), prof, one], [np.ones(nx), np.zeros(ny), one]]))
+    if velocity == "const":
+        wl = dataclasses.replace(wl, u_sep=None, u_const=np.array([0.03, 0.0 if wall != "periodic" else -0.02]))
+    return wl
+
+
+@pytest.mark.parametrize("precision", ["fp32", "fp64"])
+@pytest.mark.parametrize("nx,ny,wall,velocity", [
+    (64, 10, "periodic", "separable"), (108, 11, "periodic", "const"), (109, 150, "periodic", "separable"),
+    (163, 37, "periodic", "separable"), (301, 64, "periodic", "const"),
+    (64, 2, "node", "separable"), (107, 3, "node", "const"), (200, 33, "node", "separable"),
+    (64, 1, "bounce", "const"), (110, 2, "specular", "separable"), (162, 41, "bounce", "separable"),
+    (217, 130, "specular", "separable"), (70, 7, "specular", "const"), (90, 6, "bounce", "separable"),
+])
+def test_marching_launches_equal_one_step(nx, ny, wall, velocity, precision):
+    from paper_1404_2363_amd.solver import Solver
+    wl = _case(nx, ny, wall, velocity)
+    ref = Solver(wl, precision)
+    ref.set_variant(_one_step(ref))
+    strips = [v for v in ref.variants() if _strip(v)]
+    assert [v["steps_per_launch"] for v in strips] == [4, 5, 6]
+    want = []
+    for n in SEQ:
+        ref.step(n)
+        want.append(populations(ref.get_state().cpu().numpy(), 9, wl.nodes, precision)[0])
+    ref.close()
+    print(f"case strips {nx}x{ny} {wall} {velocity} u {precision}", flush=True)
+    for v in strips:
+        s = Solver(wl, precision)
+        s.set_variant(v)
+        assert s.variant() == v
+        for n, w in zip(SEQ, want):
+            s.step(n)
+            got = populations(s.get_state().cpu().numpy(), 9, wl.nodes, precision)[0]
+            np.testing.assert_array_equal(got, w, err_msg=f"{v} after {n}")
+        assert s.steps_done() == sum(SEQ)
+        s.close()
+
+
+@pytest.mark.parametrize("precision", ["fp32", "fp64"])
+@pytest.mark.parametrize("kind", ["walls", "periodic"])
+def test_marching_batch(kind, precision):
+    """A batch in marching launches, with budgets that end inside captured
+    blocks and odd step counts, equals one-step batched launches: states,
+    sampled moments and step counts."""
+    import torch
+    from paper_1404_2363_amd.solver import Solver
+    walls = ["specular", "bounce", "node"] if kind == "walls" else ["periodic"]
+    wls, per = [], []
+    for k, (nx, ny, budget) in enumerate([(300, 12, -1), (70, 20, 45), (160, 33, -1), (111, 16, 97), (64, 140, 17)]):
+        wls.append(_case(nx, ny, walls[k % len(walls)], "separable"))
+        per.append({"max_steps": budget, "xref0": 10.0, "xref_drift": 0.02})
+    out = []
+    for strip in (True, False):
+        s = Solver(wls, precision, per_run=per)
+        v = {"block": (64, 1), "rows_per_thread": 0, "nt_stores": False, "block_order": 1, "grid": 0,
+             "steps_per_launch": 6} if strip else \
+            next(v for v in s.variants() if v["steps_per_launch"] == 1 and v["block"] == (256, 1))
+        s.set_variant(v)
+        rec = []
+        for n in (1, 2, 3, 5, 48, 7, 31):
+            s.step(n)
+            rec += [s.phi(i).cpu().numpy() for i in range(len(wls))]
+        hist = torch.zeros((20, len(wls), 3), dtype=torch.float64, device="cuda:0")
+        s.run_sampled(100, 25, hist)
+        s.run_sampled(21, 7, hist)
+        rec += [s.phi(i).cpu().numpy() for i in range(len(wls))]
+        rec += [hist.cpu().numpy(), np.array([s.steps_done(i) for i in range(len(wls))])]
+        out.append(rec)
+        s.close()
+    print(f"case strip batch {kind} {precision}", flush=True)
+    for i, (a, b) in enumerate(zip(*out)):
+        np.testing.assert_array_equal(a, b, err_msg=str(i))
