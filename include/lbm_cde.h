@@ -282,6 +282,9 @@ int lbm_cde_set_velocity(lbm_cde_handle h, int32_t run, const double* u);
  * constant D and a constant or separable velocity (factor 1 in z) at least 64
  * nodes wide, periodic in y with at least 10 rows or bounded by walls; a
  * call's steps are divided evenly over launches of at most that many.
+ * D3Q15 runs with a constant or separable velocity, periodic or mirrored in x
+ * and y (any kind in z), take two steps per launch over blocks of columns that
+ * march along z, and start so.
  * A run that can take several steps per launch starts with 4 (64 x 24
  * tiles in FP32 where the grid allows them, else 64 x 16; 64 x 8 in FP64),
  * one of 300,000 nodes or more that can march, and a batch of as many, with a

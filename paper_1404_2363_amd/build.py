@@ -14,7 +14,8 @@ import tempfile
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 LIB = os.path.join(HERE, "liblbm_cde.so")
-SOURCES = [os.path.join(HERE, "csrc", f) for f in ("lbm_cde.hip", "strip_f32.hip", "strip_f64.hip")]
+SOURCES = [os.path.join(HERE, "csrc", f) for f in
+           ("lbm_cde.hip", "strip_f32.hip", "strip_f64.hip", "vol.hip")]
 ARCH = os.environ.get("LBM_CDE_ARCH", "gfx950")
 
 

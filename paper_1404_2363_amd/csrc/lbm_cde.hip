@@ -32,6 +32,7 @@
 #include "adjoint_fused_d2q9.hpp"
 #include "stability.hpp"
 #include "strip_d2q9.hpp"
+#include "vol.hpp"
 
 using namespace lbm;
 
@@ -838,9 +839,51 @@ Variant strip_start(const Run& r) {
   return strip_variant(best.T);
 }
 
+// Two D3Q15 steps per launch (fused_d3q15.hpp): velocity constant or
+// separable, x and y periodic or mirrored, z any kind, and 32-bit offsets
+// within a plane of nodes, with x or y walls within all the populations.
+bool vol_ok(const Run& r) {
+  if (r.d.lattice != LBM_CDE_D3Q15 || r.d.u_kind == LBM_CDE_U_FIELD) return false;
+  bool wxy = false;
+  for (int a = 0; a < 2; ++a) {
+    if (r.d.bc[a] != LBM_CDE_PERIODIC && r.d.bc[a] != LBM_CDE_SPECULAR) return false;
+    wxy |= r.d.bc[a] != LBM_CDE_PERIODIC;
+  }
+  const double plane = (double)r.d.nx * (double)r.d.ny * (double)r.elem;
+  return (wxy ? (double)r.Q * (double)r.plane * (double)r.elem : plane) < 4294967296.0 && r.d.nx < (1ll << 30) &&
+         r.d.ny < (1ll << 30) && r.d.nz < (1ll << 30);
+}
+
+template <bool DBL, int K>
+void launch_vol(const RunArgs a, hipStream_t s) {
+  vol_launch(kVolTiles[DBL ? 1 : 0][K][0], kVolTiles[DBL ? 1 : 0][K][1], DBL)(a, s);
+}
+const StepFn kVol[2][2] = {{launch_vol<false, 0>, launch_vol<false, 1>}, {launch_vol<true, 0>, launch_vol<true, 1>}};
+
+Variant vol_variant(const Run& r, int k) {
+  const auto& t = kVolTiles[r.dbl ? 1 : 0][k];
+  return Variant{t[0], t[1], 1, false, 1, 0, 2};
+}
+
+// The tile of the two that should be faster, or the one-step launch.
+Variant vol_start(const Run& r, const Variant& one) {
+  if (!vol_ok(r)) return one;
+  double cost[2];
+  for (int k = 0; k < 2; ++k) {
+    const auto& t = kVolTiles[r.dbl ? 1 : 0][k];
+    cost[k] = vol_cut(t[0], t[1], r.dbl, r.d.nx, r.d.ny, r.d.nz).cost;
+  }
+  return vol_variant(r, cost[1] < cost[0] ? 1 : 0);
+}
+
 StepFn find_step(const Run& r, const Variant& v) {
   const int p = r.dbl ? 1 : 0, w = r.walls ? 1 : 0;
   if (v.strip()) return strip_ok(r, v.fuse) && v == strip_variant(v.fuse) ? kStrip[p][v.fuse - 2] : nullptr;
+  if (v.fuse == 2 && r.d.lattice == LBM_CDE_D3Q15) {
+    for (int k = 0; k < 2; ++k)
+      if (vol_ok(r) && v == vol_variant(r, k)) return kVol[p][k];
+    return nullptr;
+  }
   if (v.fuse != 1) {
     if (v.fuse < 2 || !v.nt || !fused_ok(r, v)) return nullptr;
     for (const auto& e : kFused)
@@ -1412,6 +1455,7 @@ int init_runs(lbm_cde* h, const lbm_cde_run_desc* runs, int32_t nruns, const dou
       const Variant multi16 = Variant{64, 8, 2, true, 0, 0, 4};
       const Variant march = strip_start(r);
       if (march.fuse > 1) r.var = march;
+      else if (r.d.lattice == LBM_CDE_D3Q15) r.var = vol_start(r, r.var);
       else if (r.d.lattice == LBM_CDE_D2Q9 && !r.half && find_step(r, multi)) r.var = multi;
       else if (r.d.lattice == LBM_CDE_D2Q9 && !r.half && !r.dbl && find_step(r, multi16)) r.var = multi16;
     }
@@ -1781,6 +1825,8 @@ std::vector<Variant> run_candidates(const Run& r) {
       add(Variant{256, 1, 1, false, xcd});
     } else if (r.d.lattice == LBM_CDE_D3Q15) {
       for (const auto& e : kSteps3) add(Variant{e.bx, e.by, e.ny, e.nt, xcd});
+      if (xcd == 1 && vol_ok(r))
+        for (int k = 0; k < 2; ++k) add(vol_variant(r, k));
     } else {
       for (const auto& e : kSteps) add(Variant{e.bx, e.by, e.ny, e.nt, xcd});
       for (const auto& e : kFused) {
