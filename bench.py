@@ -68,9 +68,9 @@ def kernel_name(launch, real):
     T = launch.get("steps_per_launch", 1)
     if T == 1:
         return f"k_step_d2q9<{real}>"
-    if launch["rows_per_thread"] == 0:
-        return f"k_strip_d2q9<{real}, {T}>"
     bx, by = launch["block"]
+    if (bx, by) == (64, 1):
+        return f"k_strip_d2q9<{real}, {T}>"
     return f"k_fused_d2q9<{real}, {bx}, {by}, {launch['rows_per_thread']}, {T}>"
 
 

@@ -277,8 +277,11 @@ int lbm_cde_set_velocity(lbm_cde_handle h, int32_t run, const double* u);
  * intermediate steps of a tile and its halo in LDS (Eq. 5: a population
  * moves one node per step), so the state crosses HBM once per launch; the
  * steps left over when a call's count is not a multiple go one per launch.
- * Zero rows per thread name the launches whose waves (64 x 1) march along y
- * with the steps between in registers, 4 to 6 at a time: for such runs with a
+ * Grids of up to 512 x 512 nodes have launches of their own: 8 x 64, 16 x 64
+ * and 32 x 32 threads that take 8 steps of an 8 x 8, 16 x 16 or 32 x 32 tile,
+ * and 16 x 32 threads that take 4 of a 16 x 16 tile.  Blocks of 64 x 1 name
+ * the launches whose waves march along y with the steps between in
+ * registers, 4 to 6 at a time: for such runs with a
  * constant D and a constant or separable velocity (factor 1 in z) at least 64
  * nodes wide, periodic in y with at least 10 rows or bounded by walls; a
  * call's steps are divided evenly over launches of at most that many.
@@ -287,8 +290,10 @@ int lbm_cde_set_velocity(lbm_cde_handle h, int32_t run, const double* u);
  * march along z, and start so.
  * A run that can take several steps per launch starts with 4 (64 x 24
  * tiles in FP32 where the grid allows them, else 64 x 16; 64 x 8 in FP64),
- * one of 300,000 nodes or more that can march, and a batch of as many, with a
- * marching launch of 4 to 6; any other with one.  A batched handle has
+ * one of at most 256 small tiles with the launch of the smallest such tile (4
+ * steps with walls and between 16,384 and 49,152 nodes, else 8), one of
+ * 600,000 nodes or more (300,000 in FP64) that can march, and a batch of as
+ * many, with a marching launch of 4 to 6; any other with one.  A batched handle has
  * one variant for all its runs; the run index only has to be valid.  Results
  * are bitwise the same for every variant. */
 

@@ -34,7 +34,7 @@ __global__ __launch_bounds__(BX * BY) void k_fused_v_d2q9(const RunArgs a, char*
   // run on one XCD and its L2
   const uint32_t b = tile_of_block32(blockIdx.x, gridDim.x, a.tiles_x, 1);
   const uint32_t ntx = ((uint32_t)a.nx + BX - 1) / BX, tyi = b / ntx;
-  fused_tile<R, BX, BY, NY, T, UK, false, true, NP>(a, b - tyi * ntx, tyi, vout, vstep, store_end != 0);
+  fused_tile<R, BX, BY * NY, BX * BY, T, UK, false, true, NP>(a, b - tyi * ntx, tyi, vout, vstep, store_end != 0);
 }
 
 // Reverse steps k_hi, k_hi - 1, ..., k_hi - T + 1 of a segment: mu_in =

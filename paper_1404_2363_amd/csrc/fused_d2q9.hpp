@@ -57,25 +57,30 @@ LBM_FORCEINLINE void wall_source(const RunArgs& a, int32_t y, int32_t ny, int& p
   row_source_d2q9<EX, EY>(a, y, ny, pop, sy, dx);
 }
 
-// T steps of output tile (txi, tyi) of the run described by a; block (BX,
-// BY) threads, tile BX x (BY * NY).  With VOUT (the adjoint's forward
+// Height of the tile of a block of by thread rows: ny rows per thread, or with
+// ny < 0 -ny threads per node (the widened tile of a small output tile has
+// many times its nodes, and the block a thread for each of them).
+constexpr int tile_height(int by, int ny) { return ny > 0 ? by * ny : by / -ny; }
+
+// T steps of output tile (txi, tyi), TX x TY nodes, of the run described by
+// a, in a block of NTH threads.  With VOUT (the adjoint's forward
 // recomputation) every step also stores v = (n3 + s4 n4 / 2, n5 + s6 n6 / 2)
 // of the tile's own nodes (adjoint_v; two planes of nx ny values at
 // vout + s * vstep bytes for the launch's step s), and the final state goes to
 // memory only with store_end.
-template <typename R, int BX, int BY, int NY, int T, int UK, bool WY, bool VOUT = false, bool NP = false>
+template <typename R, int TX, int TY, int NTH, int T, int UK, bool WY, bool VOUT = false, bool NP = false>
 LBM_FORCEINLINE void fused_tile(const RunArgs& a, uint32_t txi, uint32_t tyi, char* vout = nullptr,
                                 int64_t vstep = 0, bool store_end = true) {
   static_assert(T >= 2, "one step per launch is k_step_d2q9");
-  constexpr int NTH = BX * BY, TX = BX, TY = BY * NY, RG = T - 1;
+  constexpr int RG = T - 1;
   constexpr int W0 = TX + 2 * RG, H0 = TY + 2 * RG, C0 = W0 * H0;
   constexpr int K0 = (C0 + NTH - 1) / NTH;
   static_assert(W0 <= NTH && H0 <= NTH, "one thread per staged column and row");
   __shared__ R lds[9 * C0];
   __shared__ R ucol[UK == 1 ? 2 * W0 : 1], urow[UK == 1 ? 2 * H0 : 1];
 
-  const int tid = threadIdx.y * BX + threadIdx.x;
-  // the launch's block is BX x BY: the slots below that every thread fills
+  const int tid = threadIdx.y * blockDim.x + threadIdx.x;
+  // the launch's block has NTH threads: the slots below that every thread fills
   // then need no guard, and a slot's collision waits only for its own loads
   // (a guarded slot before it would make the wait cover every load issued)
   if (tid >= NTH) __builtin_unreachable();
@@ -140,8 +145,9 @@ LBM_FORCEINLINE void fused_tile(const RunArgs& a, uint32_t txi, uint32_t tyi, ch
     }
   };
   // collision of one node at periodic image (x, y); (lx, ly) in the widened
-  // tile; st = the launch's step
-  auto collide = [&](R(&f)[9], int32_t x, int32_t y, int lx, int ly, int st) {
+  // tile; st = the launch's step; par = the node's A_xx, A_xy, A_yy if the
+  // caller has them (a D field with the same heat-flux rates everywhere)
+  auto collide = [&](R(&f)[9], int32_t x, int32_t y, int lx, int ly, int st, const R* par) {
     R ux, uy;
     if constexpr (UK == 0) {
       ux = (R)a.u_const[0];
@@ -153,7 +159,9 @@ LBM_FORCEINLINE void fused_tile(const RunArgs& a, uint32_t txi, uint32_t tyi, ch
       velocity2<R>(a, x, y, ux, uy);
     }
     if constexpr (NP) {  // per-node relaxation parameters (a D field)
-      const Rel2<R> rn = node_rel2<R>(a, (int64_t)y * nx + x);
+      const Rel2<R> rn = par && a.node_heat_const
+                             ? make_rel2<R>(par[0], par[1], par[2], (R)a.heat[0], (R)a.heat[1], a)
+                             : node_rel2<R>(a, (int64_t)y * nx + x);
       store_v(f, ux, uy, rn, x, y, lx, ly, st);
       collide_d2q9<R, 1>(f, ux, uy, phi_ref, rn);
     } else {
@@ -162,6 +170,10 @@ LBM_FORCEINLINE void fused_tile(const RunArgs& a, uint32_t txi, uint32_t tyi, ch
     }
   };
 
+  // the D field's flux block at the nodes of the slots, read once for all the
+  // steps that a slot takes (a read per step costs the tile 3 loads from the
+  // L2 behind every barrier)
+  R npar[NP ? K0 : 1][3];
   // step 1: HBM -> LDS over the whole widened tile
   {
     // the nine source planes as scalar base addresses (as the destination
@@ -200,6 +212,12 @@ LBM_FORCEINLINE void fused_tile(const RunArgs& a, uint32_t txi, uint32_t tyi, ch
       const int ly = j / W0, lx = j - ly * W0;
       const int32_t x = wrap_once(x0 + lx, nx), y = grid_row(ly);
       if (outside(y)) return;
+      if constexpr (NP) {
+        const uint32_t n = __umul24((uint32_t)y, (uint32_t)nx) + x, N = (uint32_t)nx * (uint32_t)ny;
+        const char* np = (const char*)a.node_par;
+#pragma unroll
+        for (int c = 0; c < 3; ++c) npar[k][c] = gld<R>(np + (size_t)c * N * E, n * E);
+      }
       const uint32_t xm = x == 0 ? nx - 1 : x - 1, xp = x + 1 == nx ? 0 : x + 1;
       if (!WY || (y >= 1 && y < ny - 1)) {  // the plain pull (as in gather)
         const uint32_t r0 = __umul24((uint32_t)y, (uint32_t)nx), rm = y == 0 ? rlast : r0 - nx,
@@ -265,7 +283,7 @@ LBM_FORCEINLINE void fused_tile(const RunArgs& a, uint32_t txi, uint32_t tyi, ch
       const int ly = j / W0, lx = j - ly * W0;
       const int32_t y = grid_row(ly);
       if (outside(y)) continue;
-      collide(f[k], wrap_once(x0 + lx, nx), y, lx, ly, 0);
+      collide(f[k], wrap_once(x0 + lx, nx), y, lx, ly, 0, npar[NP ? k : 0]);
 #pragma unroll
       for (int i = 0; i < 9; ++i) lds[i * C0 + j] = f[k][i];
       __builtin_amdgcn_sched_barrier(0);
@@ -306,7 +324,7 @@ LBM_FORCEINLINE void fused_tile(const RunArgs& a, uint32_t txi, uint32_t tyi, ch
     for (int k = 0; k < K0; ++k) {
       if (!in[k]) continue;
       const int lx = slx[k], ly = sly[k];
-      collide(f[k], wrap_once(x0 + lx, nx), grid_row(ly), lx, ly, s - 1);
+      collide(f[k], wrap_once(x0 + lx, nx), grid_row(ly), lx, ly, s - 1, npar[NP ? k : 0]);
 #pragma unroll
       for (int i = 0; i < 9; ++i) lds[i * C0 + ly * W0 + lx] = f[k][i];
     }
@@ -324,13 +342,14 @@ LBM_FORCEINLINE void fused_tile(const RunArgs& a, uint32_t txi, uint32_t tyi, ch
     asm volatile("" : "+s"(dpl[i]));
   }
 #pragma unroll
-  for (int k = 0; k < NY; ++k) {
-    const int lx = threadIdx.x + RG, ly = threadIdx.y + k * BY + RG;
+  for (int k = 0; k < (TX * TY + NTH - 1) / NTH; ++k) {
+    const int j = tid + k * NTH, ly = j / TX + RG, lx = j % TX + RG;
+    if (TX * TY % NTH != 0 && j >= TX * TY) break;
     const int32_t x = x0 + lx, y = y0 + ly;
     if (x >= nx || y >= ny) continue;
     R g[9];
     gather(g, lx, ly, y);
-    collide(g, x, y, lx, ly, T - 1);
+    collide(g, x, y, lx, ly, T - 1, nullptr);
     if (VOUT && !store_end) continue;
     const uint32_t off = (__umul24((uint32_t)y, (uint32_t)nx) + x) * (uint32_t)sizeof(R);
 #pragma unroll
@@ -345,7 +364,7 @@ template <typename R, int BX, int BY, int NY, int T, int UK, bool WY, bool NP>
 __global__ __launch_bounds__(BX * BY) void k_fused_d2q9(const RunArgs a) {
   const uint32_t b = tile_of_block32(blockIdx.x, gridDim.x, a.tiles_x, a.xcd_remap);
   const uint32_t tyi = fdiv(b, a.tiles_x);
-  fused_tile<R, BX, BY, NY, T, UK, WY, false, NP>(a, b - tyi * a.tiles_x.d, tyi);
+  fused_tile<R, BX, tile_height(BY, NY), BX * BY, T, UK, WY, false, NP>(a, b - tyi * a.tiles_x.d, tyi);
 }
 
 // The arguments of one step of a batched run (its compact record), for the
@@ -429,7 +448,7 @@ __global__ __launch_bounds__(BX * BY) void k_batch_fused_d2q9(const BatchRun* __
   const RunArgs a = batch_run_args<R>(br, (int)(clock[2] & 1) ^ flip);
   const uint32_t ntx = (br.nx + BX - 1) / BX, local = t - tile_start[lo];
   const uint32_t tyi = local / ntx;
-  fused_tile<R, BX, BY, NY, T, UK, WY>(a, local - tyi * ntx, tyi);
+  fused_tile<R, BX, BY * NY, BX * BY, T, UK, WY>(a, local - tyi * ntx, tyi);
 }
 
 }  // namespace lbm

@@ -29,6 +29,7 @@
 #include "adjoint_d2q9.hpp"
 #include "fp16_d2q9.hpp"
 #include "fused_d2q9.hpp"
+#include "fused_launch.hpp"
 #include "adjoint_fused_d2q9.hpp"
 #include "stability.hpp"
 #include "strip_d2q9.hpp"
@@ -68,7 +69,7 @@ size_t plane_skew() {
 // A launch variant of the step kernel: tile shape, store kind, block order,
 // for the batched persistent launch its number of blocks, and the number of
 // steps one launch takes (more than one: the LDS-blocked D2Q9 kernel, or with
-// ny = 0 the marching one).
+// 64 x 1 blocks the marching one).
 struct Variant {
   int bx, by, ny;
   bool nt;       // non-temporal (streaming) stores
@@ -79,11 +80,16 @@ struct Variant {
     return bx == o.bx && by == o.by && ny == o.ny && nt == o.nt && xcd == o.xcd && grid == o.grid &&
            fuse == o.fuse;
   }
-  bool strip() const { return ny == 0; }  // waves marching along y (strip_d2q9.hpp)
+  bool strip() const { return fuse > 1 && bx == 64 && by == 1; }  // waves marching along y (strip_d2q9.hpp)
+  int64_t height() const {  // rows of a tile
+    for (const SmallTile& t : kSmall)
+      if (bx == t.bx && by == t.by && ny == 1 && fuse == t.T) return tile_height(t.by, t.ny);
+    return (int64_t)by * ny;
+  }
 };
 
 // The marching launch of T steps.
-Variant strip_variant(int T) { return Variant{64, 1, 0, false, 1, 0, T}; }
+Variant strip_variant(int T) { return Variant{64, 1, 1, false, 1, 0, T}; }
 
 struct Run {
   lbm_cde_run_desc d;
@@ -115,6 +121,7 @@ struct Run {
   int cur = 0;         // population buffer (0/1) that holds the current state
   bool walls = false;
   Variant var{256, 1, 1, true, false};
+  Variant var4{256, 1, 1, true, false};  // four-step launches for what an eight-step variant leaves over
   Variant var1{256, 1, 1, true, false};  // one-step launches (the steps a multi-step variant leaves over)
 };
 
@@ -528,7 +535,7 @@ size_t layout(Run& r, char* base) {
 
 // Number of tile rows of a launch (y tiles times z planes).
 int64_t tile_rows(const Run& r, const Variant& v) {
-  const int64_t th = v.strip() ? 1 : (int64_t)v.by * v.ny;
+  const int64_t th = v.height();
   return (r.d.ny + th - 1) / th * r.d.nz;
 }
 
@@ -593,7 +600,7 @@ RunArgs make_args(const lbm_cde* h, const Run& r, int parity, const Variant* lau
   // tile counts of the launch's block shape (16-bit runs: the split kernels
   // tile BX x BY nodes; the literal kernel 256 x 1)
   const int64_t tbx = r.half && !r.split ? 256 : var.bx;
-  const int64_t tby = (r.half && !r.split) || var.strip() ? 1 : (int64_t)var.by * (r.half ? 1 : var.ny);
+  const int64_t tby = r.half && !r.split ? 1 : r.half ? var.by : var.height();
   a.tiles_x = make_fastdiv((uint32_t)((r.d.nx + tbx - 1) / tbx));
   a.tiles_y = make_fastdiv((uint32_t)((r.d.ny + tby - 1) / tby));
   a.rows32 = r.d.lattice == LBM_CDE_D2Q9 && !r.half && r.d.bc[0] == LBM_CDE_PERIODIC && !r.node_par &&
@@ -738,30 +745,6 @@ const SplitEntry kSplit[] = {SPLIT_ENTRY(64, 4), SPLIT_ENTRY(128, 2), SPLIT_ENTR
                              SPLIT_ENTRY(128, 4), SPLIT_ENTRY(256, 2)};
 
 
-// Several steps per launch (fused_d2q9.hpp): D2Q9 in FP64 or FP32, periodic
-// on both axes, streaming stores; tile BX x (BY * NY) nodes; the velocity
-// kind is a template argument.  A shape whose LDS (nine planes of the tile
-// widened by T - 1 nodes on every side) would exceed the 160 KiB of a CU is
-// not built for that precision.
-template <typename R, int BX, int BY, int NY, int T>
-void launch_fused(const RunArgs a, hipStream_t s) {
-  const int64_t ntx = (a.nx + BX - 1) / BX, nty = (a.ny + BY * NY - 1) / (BY * NY);
-  const dim3 g((unsigned)(ntx * nty)), b(BX, BY);
-  if (a.node_par) {  // a D field (periodic, velocity constant or separable: fused_ok)
-    if (a.u_kind == U_CONST) hipLaunchKernelGGL((k_fused_d2q9<R, BX, BY, NY, T, 0, false, true>), g, b, 0, s, a);
-    else hipLaunchKernelGGL((k_fused_d2q9<R, BX, BY, NY, T, 1, false, true>), g, b, 0, s, a);
-  } else if (a.bc[1] != LBM_CDE_PERIODIC) {  // walls in y (velocity constant or separable)
-    if (a.u_kind == U_CONST) hipLaunchKernelGGL((k_fused_d2q9<R, BX, BY, NY, T, 0, true, false>), g, b, 0, s, a);
-    else hipLaunchKernelGGL((k_fused_d2q9<R, BX, BY, NY, T, 1, true, false>), g, b, 0, s, a);
-  } else if (a.u_kind == U_CONST) {
-    hipLaunchKernelGGL((k_fused_d2q9<R, BX, BY, NY, T, 0, false, false>), g, b, 0, s, a);
-  } else if (a.u_kind == U_SEPARABLE) {
-    hipLaunchKernelGGL((k_fused_d2q9<R, BX, BY, NY, T, 1, false, false>), g, b, 0, s, a);
-  } else {
-    hipLaunchKernelGGL((k_fused_d2q9<R, BX, BY, NY, T, 2, false, false>), g, b, 0, s, a);
-  }
-}
-
 template <typename R, int BX, int BY, int NY, int T>
 constexpr StepFn fused_fn() {
   if constexpr (9 * (BX + 2 * (T - 1)) * (BY * NY + 2 * (T - 1)) * sizeof(R) <= 160 * 1024)
@@ -769,6 +752,8 @@ constexpr StepFn fused_fn() {
   else
     return nullptr;
 }
+
+StepFn find_step(const Run& r, const Variant& v);
 
 struct FusedEntry {
   int bx, by, ny, T;
@@ -793,10 +778,36 @@ bool fused_ok(const Run& r, const Variant& v) {
   return r.d.lattice == LBM_CDE_D2Q9 && !r.half && !r.split && r.d.bc[0] == LBM_CDE_PERIODIC && r.d.nz == 1 &&
          (r.d.model == LBM_CDE_MRT_A || r.d.model == LBM_CDE_MRT_B3) && !(wy && r.d.u_kind == LBM_CDE_U_FIELD) &&
          !(r.node_par && (wy || r.d.u_kind == LBM_CDE_U_FIELD)) &&
-         r.d.nx >= (int64_t)v.bx + 2 * (v.fuse - 1) && (wy || r.d.ny >= (int64_t)v.by * v.ny + 2 * (v.fuse - 1)) &&
+         r.d.nx >= (int64_t)v.bx + 2 * (v.fuse - 1) && (wy || r.d.ny >= v.height() + 2 * (v.fuse - 1)) &&
          (double)r.nodes * (double)r.elem < 4294967296.0 && r.d.nx < (1ll << 24) && r.d.ny < (1ll << 24) &&
          v.grid == 0;
 }
+
+template <bool DBL, int K>
+void launch_small(const RunArgs a, hipStream_t s) {
+  if (DBL) launch_small_f64(K, a, s);
+  else launch_small_f32(K, a, s);
+}
+const StepFn kSmallFn[2][kSmallCount] = {
+    {launch_small<false, 0>, launch_small<false, 1>, launch_small<false, 2>, launch_small<false, 3>},
+    {launch_small<true, 0>, launch_small<true, 1>, launch_small<true, 2>, launch_small<true, 3>}};
+
+Variant small_variant(int k, int xcd = 1) {
+  const SmallTile& t = kSmall[k];
+  return Variant{t.bx, t.by, 1, true, xcd, 0, t.T};
+}
+
+// The small-tile launch that a run starts with, or `other`: the smallest tile
+// of which the grid has at most one for each of the 256 CUs.  There a launch
+// takes as long as one block does, and a thread for (nearly) every node of the
+// widened tile keeps that short; eight steps share the 3-4 us that a launch
+// spends on starting, loading and storing.  Measured, us a step, against the
+// 64 x 24 (FP64 64 x 8) tiles of four steps: 128^2 FP64 0.97 (8 x 8) against
+// 2.11, FP32 0.80; 256^2 FP32 1.04 (16 x 16) against 2.25; 512^2 FP32 1.95
+// (32 x 32) against 2.70, FP64 2.87 against 3.30.  Between the 8 x 8 tiles and
+// 49,152 nodes (192 tiles of 16 x 16) runs keep four steps, in 16 x 16 tiles
+// (1.2 us at 128^2 FP32), as do those with walls.
+Variant small_start(const Run& r, const Variant& other);
 
 // The marching launch takes the runs of the tile kernel with a constant D, a
 // constant or separable velocity (unit z factors), at least a wave's columns
@@ -821,18 +832,31 @@ const StepFn kStrip[2][kStripMax - 1] = {{launch_strip<false, 2>, launch_strip<f
                                           launch_strip<true, 5>, launch_strip<true, 6>}};
 
 // The marching launch that a run starts with (fuse 1: none): large grids whose
-// width fills the strips.  Below about 300,000 nodes the waves of a launch
-// have few rows each and the halo rows dominate (512^2: 17.3 us for six steps
-// in FP32 against 15.6 us for eight in LDS tiles; at 724^2 the tile kernel
-// takes 3.9 us a step, the march 3.8, in FP64 7.8 against 4.8); a strip that
-// keeps less than 70 % of its lanes costs more than the tiles' halo.
-constexpr int64_t kStripNodes = 300000;
+// width fills the strips.  On smaller grids the waves of a launch have few rows
+// each and the halo rows dominate.  FP32: 3007 x 127 between walls 4.65 us a
+// step against 4.05 in LDS tiles, 724^2 3.8 against 3.9, 3000 x 301 5.5
+// against 6.0, 1024^2 5.6 against 6.2; FP64: 512^2 3.4 against 2.9, 724^2 4.8
+// against 7.8.  A strip that keeps less than 70 % of its lanes costs more than
+// the tiles' halo.
+constexpr int64_t strip_nodes(bool dbl) { return dbl ? 300000 : 600000; }
+
+Variant small_start(const Run& r, const Variant& other) {
+  for (int k : {0, 1, 3, 2}) {
+    const Variant v = small_variant(k);
+    const int64_t tiles = (r.d.nx + v.bx - 1) / v.bx * ((r.d.ny + v.height() - 1) / v.height());
+    if (tiles > 256 || !find_step(r, v)) continue;
+    if (k == 1 && r.nodes < 49152) continue;
+    if (r.d.bc[1] != LBM_CDE_PERIODIC && k != 3) continue;
+    return v;
+  }
+  return other;
+}
 
 Variant strip_start(const Run& r) {
   StripCut best{1, 0, 1e300};
   for (int T = 4; T <= kStripMax; ++T) {
     const int64_t nsx = (r.d.nx + strip_width(T) - 1) / strip_width(T);
-    if (!strip_ok(r, T) || r.nodes < kStripNodes || 10 * r.d.nx < 7 * 64 * nsx) continue;
+    if (!strip_ok(r, T) || r.nodes < strip_nodes(r.dbl) || 10 * r.d.nx < 7 * 64 * nsx) continue;
     const StripCut c = strip_cut_run(T, r.d.nx, r.d.ny, r.dbl);
     if (c.cost < best.cost) best = c;
   }
@@ -888,6 +912,8 @@ StepFn find_step(const Run& r, const Variant& v) {
     if (v.fuse < 2 || !v.nt || !fused_ok(r, v)) return nullptr;
     for (const auto& e : kFused)
       if (e.bx == v.bx && e.by == v.by && e.ny == v.ny && e.T == v.fuse) return e.fn[p];
+    for (int k = 0; k < kSmallCount; ++k)
+      if (v == small_variant(k, v.xcd)) return kSmallFn[p][k];
     return nullptr;
   }
   if (r.split) {
@@ -940,14 +966,17 @@ int64_t enqueue_run(lbm_cde* h, Run& r, int64_t n, hipStream_t s, bool even = fa
     return (int64_t)parts.size();
   }
   int64_t q = T > 1 ? n / T : 0, rest = n - q * T;
-  if (even && T > 1 && q > 0 && ((q + rest) & 1)) {
+  const int64_t q4 = T > 4 && r.var4.fuse == 4 ? rest / 4 : 0;
+  rest -= 4 * q4;
+  if (even && T > 1 && q > 0 && ((q + q4 + rest) & 1)) {
     q -= 1;
     rest += T;
   }
   for (int64_t k = 0; k < q; ++k) launch_variant(h, r, r.var, s);
+  for (int64_t k = 0; k < q4; ++k) launch_variant(h, r, r.var4, s);
   const Variant& v1 = T > 1 ? r.var1 : r.var;
   for (int64_t k = 0; k < rest; ++k) launch_variant(h, r, v1, s);
-  return q + rest;
+  return q + q4 + rest;
 }
 
 // Steps of a captured graph of a handle whose runs step on their own.
@@ -1355,7 +1384,7 @@ Variant batch_strip_start(const lbm_cde* h) {
       lanes += (r.d.nx + strip_width(T) - 1) / strip_width(T) * 64;
       kept += r.d.nx;
     }
-    if (nodes < kStripNodes || 10 * kept < 7 * lanes || !find_batch_fused(h, strip_variant(T))) continue;
+    if (nodes < strip_nodes(h->runs[0].dbl) || 10 * kept < 7 * lanes || !find_batch_fused(h, strip_variant(T))) continue;
     const StripCut c = strip_cut_batch(h, T);
     if (c.cost < best.cost) best = c;
   }
@@ -1370,7 +1399,7 @@ int apply_batch_fused(lbm_cde* h, const Variant& v) {
   const int32_t nruns = (int32_t)h->runs.size();
   const size_t list = align_up(sizeof(uint32_t) * (nruns + 1));
   for (int j = 0; v.fuse > 1 && j < (v.strip() ? kStripMax - 1 : 1); ++j) {
-    int64_t tw = v.bx, th = (int64_t)v.by * v.ny;
+    int64_t tw = v.bx, th = v.height();
     if (v.strip()) {
       tw = strip_width(j + 2);
       th = h->strip_rows[j] = strip_cut_batch(h, j + 2).L;
@@ -1453,11 +1482,16 @@ int init_runs(lbm_cde* h, const lbm_cde_run_desc* runs, int32_t nruns, const dou
       // 4 steps, XCD-contiguous order in FP64)
       const Variant multi = r.dbl ? Variant{64, 4, 2, true, 1, 0, 4} : Variant{64, 12, 2, true, 1, 0, 4};
       const Variant multi16 = Variant{64, 8, 2, true, 0, 0, 4};
+      if (r.d.lattice == LBM_CDE_D2Q9 && !r.half) {
+        const Variant tile = find_step(r, multi) ? multi : multi16;
+        if (find_step(r, tile)) r.var = small_start(r, tile);
+        else r.var = small_start(r, r.var);
+        // what an eight-step launch leaves over goes in 16 x 16 tiles
+        r.var4 = find_step(r, small_variant(3)) ? small_variant(3) : r.var1;
+      }
       const Variant march = strip_start(r);
       if (march.fuse > 1) r.var = march;
       else if (r.d.lattice == LBM_CDE_D3Q15) r.var = vol_start(r, r.var);
-      else if (r.d.lattice == LBM_CDE_D2Q9 && !r.half && find_step(r, multi)) r.var = multi;
-      else if (r.d.lattice == LBM_CDE_D2Q9 && !r.half && !r.dbl && find_step(r, multi16)) r.var = multi16;
     }
     if (r.split && h->env16_set) r.var = h->env16;
     if (h->env_variant && !r.half) r.var = r.d.lattice == LBM_CDE_D3Q15 ? h->env3 : h->env;
@@ -1828,6 +1862,8 @@ std::vector<Variant> run_candidates(const Run& r) {
       if (xcd == 1 && vol_ok(r))
         for (int k = 0; k < 2; ++k) add(vol_variant(r, k));
     } else {
+      for (int k = 0; k < kSmallCount; ++k)
+        if (xcd == 1 && find_step(r, small_variant(k))) add(small_variant(k));
       for (const auto& e : kSteps) add(Variant{e.bx, e.by, e.ny, e.nt, xcd});
       for (const auto& e : kFused) {
         const Variant c{e.bx, e.by, e.ny, true, xcd, 0, e.T};
