@@ -353,7 +353,7 @@ LBM_FORCEINLINE void fused_tile(const RunArgs& a, uint32_t txi, uint32_t tyi, ch
     if (VOUT && !store_end) continue;
     const uint32_t off = (__umul24((uint32_t)y, (uint32_t)nx) + x) * (uint32_t)sizeof(R);
 #pragma unroll
-    for (int i = 0; i < 9; ++i) gst<R, true>(dpl[i], off, g[i]);
+    for (int i = 0; i < 9; ++i) gst<R, !VOUT>(dpl[i], off, g[i]);
   }
 }
 

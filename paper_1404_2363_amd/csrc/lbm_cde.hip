@@ -2001,41 +2001,80 @@ void launch_step_v(const Run& r, const RunArgs& a, void* v, bool store, hipStrea
 
 // Several steps per launch in a checkpoint segment (adjoint_fused_d2q9.hpp):
 // the forward recomputation with v, and the reverse sweep.
-template <typename R, int BX, int BY, int NY, int T>
+template <typename R, int TX, int TY, int NTH, int T>
 void launch_fused_v(const RunArgs& a, char* vout, int64_t vstep, bool store, hipStream_t s) {
-  const unsigned blocks = (unsigned)(((a.nx + BX - 1) / BX) * ((a.ny + BY * NY - 1) / (BY * NY)));
-  const dim3 g(blocks), b(BX, BY);
+  const dim3 g((unsigned)(((a.nx + TX - 1) / TX) * ((a.ny + TY - 1) / TY))), b(NTH);
+  auto go = [&](auto k) { hipLaunchKernelGGL(k, g, b, 0, s, a, vout, vstep, (int)store); };
   if (a.node_par) {  // velocity constant or separable (fused_ok)
-    if (a.u_kind == U_CONST)
-      hipLaunchKernelGGL((k_fused_v_d2q9<R, BX, BY, NY, T, 0, true>), g, b, 0, s, a, vout, vstep, (int)store);
-    else
-      hipLaunchKernelGGL((k_fused_v_d2q9<R, BX, BY, NY, T, 1, true>), g, b, 0, s, a, vout, vstep, (int)store);
+    if (a.u_kind == U_CONST) go(k_fused_v_d2q9<R, TX, TY, NTH, T, 0, true>);
+    else go(k_fused_v_d2q9<R, TX, TY, NTH, T, 1, true>);
   } else if (a.u_kind == U_CONST) {
-    hipLaunchKernelGGL((k_fused_v_d2q9<R, BX, BY, NY, T, 0, false>), g, b, 0, s, a, vout, vstep, (int)store);
+    go(k_fused_v_d2q9<R, TX, TY, NTH, T, 0, false>);
   } else if (a.u_kind == U_SEPARABLE) {
-    hipLaunchKernelGGL((k_fused_v_d2q9<R, BX, BY, NY, T, 1, false>), g, b, 0, s, a, vout, vstep, (int)store);
+    go(k_fused_v_d2q9<R, TX, TY, NTH, T, 1, false>);
   } else {
-    hipLaunchKernelGGL((k_fused_v_d2q9<R, BX, BY, NY, T, 2, false>), g, b, 0, s, a, vout, vstep, (int)store);
+    go(k_fused_v_d2q9<R, TX, TY, NTH, T, 2, false>);
   }
 }
 
-template <typename R, int BX, int BY, int NY, int T>
+template <typename R, int TX, int TY, int NTH, int T>
 void launch_fused_adj(const RunArgs& a, const char* v_hi, int64_t vstep, const void* mu_in, void* mu_out,
                       double* grad, float* part, double inv_kappa, bool fold, hipStream_t s) {
-  const unsigned blocks = (unsigned)(((a.nx + BX - 1) / BX) * ((a.ny + BY * NY - 1) / (BY * NY)));
-  if (a.node_par)
-    hipLaunchKernelGGL((k_fused_adj_d2q9<R, BX, BY, NY, T, true>), dim3(blocks), dim3(BX, BY), 0, s, a, v_hi, vstep,
-                       (const R*)mu_in, (R*)mu_out, grad, part, inv_kappa, (int)fold);
-  else
-    hipLaunchKernelGGL((k_fused_adj_d2q9<R, BX, BY, NY, T, false>), dim3(blocks), dim3(BX, BY), 0, s, a, v_hi,
-                       vstep, (const R*)mu_in, (R*)mu_out, grad, part, inv_kappa, (int)fold);
+  const dim3 g((unsigned)(((a.nx + TX - 1) / TX) * ((a.ny + TY - 1) / TY))), b(NTH);
+  auto go = [&](auto k) {
+    hipLaunchKernelGGL(k, g, b, 0, s, a, v_hi, vstep, (const R*)mu_in, (R*)mu_out, grad, part, inv_kappa, (int)fold);
+  };
+  if (a.node_par) {
+    if (a.u_kind == U_CONST) go(k_fused_adj_d2q9<R, TX, TY, NTH, T, 0, true>);
+    else go(k_fused_adj_d2q9<R, TX, TY, NTH, T, 1, true>);
+  } else if (a.u_kind == U_CONST) {
+    go(k_fused_adj_d2q9<R, TX, TY, NTH, T, 0, false>);
+  } else {
+    go(k_fused_adj_d2q9<R, TX, TY, NTH, T, 2, false>);
+  }
 }
 
-// The shape of the multi-step adjoint launches: FP32 64 x 16 tiles with 4
-// steps, FP64 64 x 8 tiles with 3 (the reverse kernel adds the tile's
-// running gradient sums to the LDS of the forward one).
-Variant adjoint_multi_variant(const Run& r) {
-  return r.dbl ? Variant{64, 4, 2, true, 0, 0, 3} : Variant{64, 8, 2, true, 0, 0, 4};
+// The tile of a run's multi-step adjoint launches (T = 0: it takes none).  A
+// grid of at most 256 tiles of 16 x 16 nodes (one per CU) is bound by the
+// serial chain of a launch, not by the chip's arithmetic: it takes those, a
+// thread for every node of the widened tile and eight steps (113 x 200 FP32,
+// 400 steps backward: 1.42 ms, with the large tile 2.02; FP64 1.74 and 2.34).
+// Larger grids take tiles whose widened rows are one wave wide, 58 x 16 with
+// two nodes per thread (FP64 58 x 10, whose 1024 nodes fill two 512-thread
+// blocks' LDS per CU), and four steps: at 512^2 small tiles' recomputed rings
+// cost more than they hide (FP32 2.81 ms against 2.66, FP64 5.16 and 3.98;
+// four concurrent conditions 11.0 and 7.5, 19.3 and 13.1).
+struct AdjTile {
+  int tx, ty, nth, T;
+};
+constexpr AdjTile kAdjSmall{16, 16, 960, 8}, kAdjLarge32{58, 16, 704, 4}, kAdjLarge64{58, 10, 512, 4};
+
+AdjTile adjoint_tile(const Run& r) {
+  auto fits = [&](const AdjTile& t) { return !r.walls && fused_ok(r, Variant{t.tx, t.ty, 1, true, 0, 0, t.T}); };
+  const AdjTile large = r.dbl ? kAdjLarge64 : kAdjLarge32;
+  if (((r.d.nx + 15) / 16) * ((r.d.ny + 15) / 16) <= 256 && fits(kAdjSmall)) return kAdjSmall;
+  return fits(large) ? large : AdjTile{0, 0, 0, 0};
+}
+
+template <int TX, int TY, int NTH, int STEPS>
+struct TileConst {
+  static constexpr AdjTile v{TX, TY, NTH, STEPS};
+};
+
+// go(R(), TileConst) of the run's precision and tile.
+template <typename Go>
+void adjoint_dispatch(const Run& r, const AdjTile& t, Go go) {
+  using Small = TileConst<kAdjSmall.tx, kAdjSmall.ty, kAdjSmall.nth, kAdjSmall.T>;
+  using L32 = TileConst<kAdjLarge32.tx, kAdjLarge32.ty, kAdjLarge32.nth, kAdjLarge32.T>;
+  using L64 = TileConst<kAdjLarge64.tx, kAdjLarge64.ty, kAdjLarge64.nth, kAdjLarge64.T>;
+  if (t.T == kAdjSmall.T) {
+    if (r.dbl) go(double(), Small());
+    else go(float(), Small());
+  } else if (r.dbl) {
+    go(double(), L64());
+  } else {
+    go(float(), L32());
+  }
 }
 
 // Scratch of a segment of K steps: two ping-pong states, v of every step
@@ -2524,10 +2563,10 @@ int lbm_cde_adjoint_segment(lbm_cde_handle h, int32_t run, const void* ckpt, int
   bool mid_inj = false;
   if (inj)
     for (int k = 0; k + 1 < K; ++k) mid_inj = mid_inj || inj[k];
-  const Variant av = adjoint_multi_variant(*r);
-  bool multi = K >= 2 && !mid_inj && !r->walls && fused_ok(*r, av);
+  const AdjTile tile = adjoint_tile(*r);
+  bool multi = K >= 2 && !mid_inj && tile.T > 0;
   if (const char* e = std::getenv("LBM_CDE_ADJ_FUSED")) multi = multi && std::atoi(e) != 0;
-  const int TA = multi ? av.fuse : 1;
+  const int TA = multi ? tile.T : 1;
   std::vector<std::pair<int, int>> fw, rv;  // (first / highest step, steps)
   for (int k = 0; k < K;) {
     const int n = k + TA <= K ? TA : 1;
@@ -2550,10 +2589,11 @@ int lbm_cde_adjoint_segment(lbm_cde_handle h, int32_t run, const void* ckpt, int
     if (n == 1) {
       if (r->dbl) launch_step_v<double>(*r, a, v, store, s);
       else launch_step_v<float>(*r, a, v, store, s);
-    } else if (r->dbl) {
-      launch_fused_v<double, 64, 4, 2, 3>(a, v, (int64_t)L.v_step, store, s);
     } else {
-      launch_fused_v<float, 64, 8, 2, 4>(a, v, (int64_t)L.v_step, store, s);
+      auto go = [&](auto real, auto t) {
+        launch_fused_v<decltype(real), t.v.tx, t.v.ty, t.v.nth, t.v.T>(a, v, (int64_t)L.v_step, store, s);
+      };
+      adjoint_dispatch(*r, tile, go);
     }
   };
   // reverse launch: steps k, k-1, .., k-n+1: mu_{k+1} (cur) -> mu_{k-n+1}
@@ -2571,10 +2611,11 @@ int lbm_cde_adjoint_segment(lbm_cde_handle h, int32_t run, const void* ckpt, int
     } else {
       const char* v_hi = segc + L.v + (size_t)k * L.v_step;
       const bool fold = k - n + 1 == 0;
-      if (r->dbl)
-        launch_fused_adj<double, 64, 4, 2, 3>(a, v_hi, (int64_t)L.v_step, cur, nxt, grad, part, inv_kappa, fold, s);
-      else
-        launch_fused_adj<float, 64, 8, 2, 4>(a, v_hi, (int64_t)L.v_step, cur, nxt, grad, part, inv_kappa, fold, s);
+      auto go = [&](auto real, auto t) {
+        launch_fused_adj<decltype(real), t.v.tx, t.v.ty, t.v.nth, t.v.T>(a, v_hi, (int64_t)L.v_step, cur, nxt, grad,
+                                                                        part, inv_kappa, fold, s);
+      };
+      adjoint_dispatch(*r, tile, go);
     }
   };
   // the forward launches after the first, from buffer P[1]
@@ -2596,12 +2637,17 @@ int lbm_cde_adjoint_segment(lbm_cde_handle h, int32_t run, const void* ckpt, int
     return cur;
   };
   const size_t sb = (size_t)r->Q * r->plane * r->elem;
-  // Graphs: with K >= 2 and no injection before the segment's last step,
-  // everything but the first forward launch (which reads the caller's
-  // checkpoint) and the first reverse step (which reads the injection) has
-  // the same arguments in every call with the same K and buffers: those two
-  // are launched directly and the rest replayed from two captured graphs.
-  bool graphs = K >= 2 && !mid_inj;
+  // Graphs: with K >= 2, one step per launch and no injection before the
+  // segment's last step, everything but the first forward launch (which reads
+  // the caller's checkpoint) and the first reverse step (which reads the
+  // injection) has the same arguments in every call with the same K and
+  // buffers: those two are launched directly and the rest replayed from two
+  // captured graphs (four conditions of 113 x 200 with walls, 2000 steps
+  // backward: 26 ms, launched one by one 60 ms).  Multi-step launches are few
+  // and last longer than the host takes to issue one: captured, the same
+  // without walls took 9.4 ms and 9.6 ms directly, and for 400 steps at 512^2
+  // the capture cost 4 % (8.15 ms, directly 7.81 ms).
+  bool graphs = K >= 2 && !mid_inj && !multi;
   if (const char* e = std::getenv("LBM_CDE_ADJ_GRAPHS")) graphs = graphs && std::atoi(e) != 0;
   if (!graphs) {
     fwd(fw[0].first, fw[0].second, ckpt, P[1], h->stream);
@@ -2619,7 +2665,7 @@ int lbm_cde_adjoint_segment(lbm_cde_handle h, int32_t run, const void* ckpt, int
   }
   auto graph = [&](int which, auto body) -> hipGraphExec_t {
     const auto key = std::make_tuple(run, K, (const void*)seg, (const void*)mu, (const void*)mu_tmp,
-                                     (const void*)grad, which + 2 * TA);
+                                     (const void*)grad, which);
     auto it = h->adj_graphs.find(key);
     if (it != h->adj_graphs.end()) return it->second;
     if (h->adj_graphs.size() >= kMaxAdjGraphs) {  // callers that change buffers every call
