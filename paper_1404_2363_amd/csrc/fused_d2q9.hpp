@@ -331,7 +331,11 @@ LBM_FORCEINLINE void fused_tile(const RunArgs& a, uint32_t txi, uint32_t tyi, ch
     __syncthreads();
   }
 
-  // step T: LDS -> HBM for the tile's own nodes
+  // step T: LDS -> HBM for the tile's own nodes.  Streaming stores where rows
+  // are whole cache lines (600 x 480 FP32 in 64 x 24 tiles: 2.40 us a step,
+  // stored plainly 2.56) or the state is small; 32-node rows start and end
+  // inside lines that the caches should gather (512^2 in 32 x 32 tiles: FP32
+  // 2.05 us streamed, 1.99 plainly, FP64 3.00 and 2.92).
   // the nine destination planes as scalar base addresses (the empty asm keeps
   // each in scalar registers and out of the per-node address arithmetic, so
   // a store takes the base-plus-32-bit-offset form with no vector add)
@@ -353,7 +357,7 @@ LBM_FORCEINLINE void fused_tile(const RunArgs& a, uint32_t txi, uint32_t tyi, ch
     if (VOUT && !store_end) continue;
     const uint32_t off = (__umul24((uint32_t)y, (uint32_t)nx) + x) * (uint32_t)sizeof(R);
 #pragma unroll
-    for (int i = 0; i < 9; ++i) gst<R, !VOUT>(dpl[i], off, g[i]);
+    for (int i = 0; i < 9; ++i) gst<R, !VOUT && TX != 32>(dpl[i], off, g[i]);
   }
 }
 

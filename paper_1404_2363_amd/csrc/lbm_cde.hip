@@ -806,7 +806,9 @@ Variant small_variant(int k, int xcd = 1) {
 // 2.11, FP32 0.80; 256^2 FP32 1.04 (16 x 16) against 2.25; 512^2 FP32 1.95
 // (32 x 32) against 2.70, FP64 2.87 against 3.30.  Between the 8 x 8 tiles and
 // 49,152 nodes (192 tiles of 16 x 16) runs keep four steps, in 16 x 16 tiles
-// (1.2 us at 128^2 FP32), as do those with walls.
+// (1.2 us at 128^2 FP32), as do those with walls up to two tiles per CU
+// (400 x 300, 475 tiles: FP32 1.91 us a step, 64 x 16 tiles 2.42; FP64 2.30
+// and, 64 x 8 tiles, 3.31; from three tiles per CU on the large ones win).
 Variant small_start(const Run& r, const Variant& other);
 
 // The marching launch takes the runs of the tile kernel with a constant D, a
@@ -844,15 +846,41 @@ Variant small_start(const Run& r, const Variant& other) {
   for (int k : {0, 1, 3, 2}) {
     const Variant v = small_variant(k);
     const int64_t tiles = (r.d.nx + v.bx - 1) / v.bx * ((r.d.ny + v.height() - 1) / v.height());
-    if (tiles > 256 || !find_step(r, v)) continue;
+    const bool walls = r.d.bc[1] != LBM_CDE_PERIODIC;
+    if (tiles > (walls ? 512 : 256) || !find_step(r, v)) continue;
     if (k == 1 && r.nodes < 49152) continue;
-    if (r.d.bc[1] != LBM_CDE_PERIODIC && k != 3) continue;
+    if (walls && k != 3) continue;
     return v;
   }
   return other;
 }
 
+// The large tile that a run starts with, four steps per launch: 64 columns and
+// 24 rows, or 16 (FP64 8).  A launch lasts as long as the CU with the most
+// tiles: with t tiles that is ceil(t / 256), each a time of about its rows.
+// FP32, us a step in 64 x 24 and 64 x 16 tiles: 600 x 480 2.45 and 2.82 (1 and
+// 2 tiles on the fullest CU), 700 x 600 3.66 and 3.13 (2 and 2), 760^2 4.02
+// and 4.81 (2 and 3), 300^2 between walls 2.57 and 2.36 (1 and 1).  A D field
+// needs registers that 768 threads do not have: equal rows go to 64 x 16
+// (1500 x 1400 17.2 and 13.5).  FP64 takes the 64 x 24 tile, whose LDS fills a
+// CU, where one per CU is enough and there would be three or more of 64 x 8:
+// 600 x 480 4.19 and 4.84, 2000 x 150 between walls 4.45 and 5.74 (marching
+// 5.46), 640 x 480 4.25 and 4.93 (marching 4.37); 700 x 600 7.70 and 6.03.
+constexpr Variant kTile24{64, 12, 2, true, 1, 0, 4}, kTile16{64, 8, 2, true, 1, 0, 4}, kTile8{64, 4, 2, true, 1, 0, 4};
+
+int64_t tiles_per_cu(const Run& r, const Variant& v) {
+  return ((r.d.nx + v.bx - 1) / v.bx * ((r.d.ny + v.height() - 1) / v.height()) + 255) / 256;
+}
+
+Variant tile_start(const Run& r) {
+  const int64_t n24 = tiles_per_cu(r, kTile24), n16 = tiles_per_cu(r, kTile16), n8 = tiles_per_cu(r, kTile8);
+  const bool tall = r.dbl ? n24 == 1 && n8 >= 3 : 24 * n24 < 16 * n16 || (24 * n24 == 16 * n16 && !r.node_par);
+  if (tall && find_step(r, kTile24)) return kTile24;
+  return r.dbl ? kTile8 : kTile16;
+}
+
 Variant strip_start(const Run& r) {
+  if (r.dbl && tile_start(r) == kTile24) return strip_variant(1);
   StripCut best{1, 0, 1e300};
   for (int T = 4; T <= kStripMax; ++T) {
     const int64_t nsx = (r.d.nx + strip_width(T) - 1) / strip_width(T);
@@ -1478,12 +1506,9 @@ int init_runs(lbm_cde* h, const lbm_cde_run_desc* runs, int32_t nruns, const dou
     }
     {
       // runs that can take several steps per launch do so by default: large
-      // ones six by the marching kernel, the others four (64 x 24 tiles, 4 steps, XCD-contiguous order in FP32, else 64 x 16; 64 x 8,
-      // 4 steps, XCD-contiguous order in FP64)
-      const Variant multi = r.dbl ? Variant{64, 4, 2, true, 1, 0, 4} : Variant{64, 12, 2, true, 1, 0, 4};
-      const Variant multi16 = Variant{64, 8, 2, true, 0, 0, 4};
+      // ones by the marching kernel, the others in tiles
       if (r.d.lattice == LBM_CDE_D2Q9 && !r.half) {
-        const Variant tile = find_step(r, multi) ? multi : multi16;
+        const Variant tile = tile_start(r);
         if (find_step(r, tile)) r.var = small_start(r, tile);
         else r.var = small_start(r, r.var);
         // what an eight-step launch leaves over goes in 16 x 16 tiles
