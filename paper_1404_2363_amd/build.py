@@ -15,7 +15,8 @@ import tempfile
 HERE = os.path.dirname(os.path.abspath(__file__))
 LIB = os.path.join(HERE, "liblbm_cde.so")
 SOURCES = [os.path.join(HERE, "csrc", f) for f in
-           ("lbm_cde.hip", "small_f32.hip", "small_f64.hip", "strip_f32.hip", "strip_f64.hip", "vol.hip")]
+           ("lbm_cde.hip", "box_f32.hip", "box_f64.hip", "small_f32.hip", "small_f64.hip", "strip_f32.hip",
+            "strip_f64.hip", "vol.hip")]
 ARCH = os.environ.get("LBM_CDE_ARCH", "gfx950")
 
 

@@ -19,7 +19,8 @@
 // instead of per step; the price is the recomputed rings (the widened tiles'
 // extra collisions) and LDS traffic.  x is periodic: halo nodes take periodic
 // images, which needs nx >= TX + 2(T-1) (one wrap per coordinate).  y is
-// periodic the same way (ny >= TY + 2(T-1)) or, with WY, bounded by walls:
+// periodic the same way (ny >= TY + 2(T-1)) or, with WY (and WX: both axes),
+// bounded by walls:
 // rows beyond a wall are not computed, and a population whose source lies
 // beyond it takes the wall rule's source (the node itself or its neighbour
 // along or inside the wall, all within one node: row_source_d2q9), from LDS
@@ -57,10 +58,34 @@ LBM_FORCEINLINE void wall_source(const RunArgs& a, int32_t y, int32_t ny, int& p
   row_source_d2q9<EX, EY>(a, y, ny, pop, sy, dx);
 }
 
+// Source of population I at node (x, y) of a box with halfway walls on both
+// axes (an on-node wall has a periodic axis beside it): (population, shift), as
+// pull_index_d2q9.
+template <int I>
+LBM_FORCEINLINE void box_source(const RunArgs& a, int32_t x, int32_t y, int32_t nx, int32_t ny, int& pop, int& dx,
+                                int& dy) {
+  constexpr int EX = I == 1 || I == 5 || I == 8 ? 1 : (I == 3 || I == 6 || I == 7 ? -1 : 0);
+  constexpr int EY = I == 2 || I == 5 || I == 6 ? 1 : (I == 4 || I == 7 || I == 8 ? -1 : 0);
+  const bool cx = EX != 0 && (uint32_t)(x - EX) >= (uint32_t)nx;
+  const bool cy = EY != 0 && (uint32_t)(y - EY) >= (uint32_t)ny;
+  const bool bounce = (cx && a.bc[0] == LBM_CDE_BOUNCE_BACK) || (cy && a.bc[1] == LBM_CDE_BOUNCE_BACK);
+  dx = bounce || cx ? 0 : -EX;
+  dy = bounce || cy ? 0 : -EY;
+  pop = pop_of_d2q9(bounce || cx ? -EX : EX, bounce || cy ? -EY : EY);
+}
+
 // Height of the tile of a block of by thread rows: ny rows per thread, or with
 // ny < 0 -ny threads per node (the widened tile of a small output tile has
 // many times its nodes, and the block a thread for each of them).
 constexpr int tile_height(int by, int ny) { return ny > 0 ? by * ny : by / -ny; }
+
+// N values of a block's LDS; the two forms of a tile in one kernel (box_tile)
+// share them.
+template <typename R, int N, int ID>
+LBM_FORCEINLINE R* tile_lds() {
+  __shared__ R m[N];
+  return m;
+}
 
 // T steps of output tile (txi, tyi), TX x TY nodes, of the run described by
 // a, in a block of NTH threads.  With VOUT (the adjoint's forward
@@ -68,7 +93,8 @@ constexpr int tile_height(int by, int ny) { return ny > 0 ? by * ny : by / -ny; 
 // of the tile's own nodes (adjoint_v; two planes of nx ny values at
 // vout + s * vstep bytes for the launch's step s), and the final state goes to
 // memory only with store_end.
-template <typename R, int TX, int TY, int NTH, int T, int UK, bool WY, bool VOUT = false, bool NP = false>
+template <typename R, int TX, int TY, int NTH, int T, int UK, bool WY, bool VOUT = false, bool NP = false,
+          bool WX = false>
 LBM_FORCEINLINE void fused_tile(const RunArgs& a, uint32_t txi, uint32_t tyi, char* vout = nullptr,
                                 int64_t vstep = 0, bool store_end = true) {
   static_assert(T >= 2, "one step per launch is k_step_d2q9");
@@ -76,8 +102,9 @@ LBM_FORCEINLINE void fused_tile(const RunArgs& a, uint32_t txi, uint32_t tyi, ch
   constexpr int W0 = TX + 2 * RG, H0 = TY + 2 * RG, C0 = W0 * H0;
   constexpr int K0 = (C0 + NTH - 1) / NTH;
   static_assert(W0 <= NTH && H0 <= NTH, "one thread per staged column and row");
-  __shared__ R lds[9 * C0];
-  __shared__ R ucol[UK == 1 ? 2 * W0 : 1], urow[UK == 1 ? 2 * H0 : 1];
+  R* lds = tile_lds<R, 9 * C0, 0>();
+  R* ucol = tile_lds<R, UK == 1 ? 2 * W0 : 1, 1>();
+  R* urow = tile_lds<R, UK == 1 ? 2 * H0 : 1, 2>();
 
   const int tid = threadIdx.y * blockDim.x + threadIdx.x;
   // the launch's block has NTH threads: the slots below that every thread fills
@@ -102,15 +129,39 @@ LBM_FORCEINLINE void fused_tile(const RunArgs& a, uint32_t txi, uint32_t tyi, ch
 
   // row of the widened tile -> row of the grid (periodic image; with walls the
   // row itself, which may lie beyond a wall and is then skipped)
+  // and columns the same way
   auto grid_row = [&](int ly) -> int32_t { return WY ? y0 + ly : wrap_once(y0 + ly, ny); };
-  auto outside = [&](int32_t y) { return WY && (y < 0 || y >= ny); };
-  // LDS gather of the nine populations of local node (lx, ly), grid row y
-  auto gather = [&](R(&f)[9], int lx, int ly, int32_t y) {
-    // rows 1 .. ny - 2 pull from rows inside the walls: there the wall rule
-    // is the plain pull, and only the two rows next to a wall need it
-    if (!WY || (y >= 1 && y < ny - 1)) {
+  auto grid_col = [&](int lx) -> int32_t { return WX ? x0 + lx : wrap_once(x0 + lx, nx); };
+  auto outside = [&](int32_t x, int32_t y) {
+    return (WY && (y < 0 || y >= ny)) || (WX && (x < 0 || x >= nx));
+  };
+  // nodes off the walls pull from nodes inside them: there the wall rule is
+  // the plain pull, and only the rows and columns next to a wall need it
+  auto plain = [&](int32_t x, int32_t y) {
+    return (!WY || (y >= 1 && y < ny - 1)) && (!WX || (x >= 1 && x < nx - 1));
+  };
+  // LDS gather of the nine populations of local node (lx, ly), grid node (x, y)
+  auto gather = [&](R(&f)[9], int lx, int ly, int32_t x, int32_t y) {
+    if (plain(x, y)) {
 #pragma unroll
       for (int i = 0; i < 9; ++i) f[i] = lds[i * C0 + (ly - kEy9[i]) * W0 + (lx - kEx9[i])];
+    } else if constexpr (WX) {
+#define LBM_FUSED_BOX_PULL(I)                                      \
+  {                                                                \
+    int pop, dx, dy;                                               \
+    box_source<I>(a, x, y, nx, ny, pop, dx, dy);                   \
+    f[I] = lds[pop * C0 + (ly + dy) * W0 + (lx + dx)];             \
+  }
+      LBM_FUSED_BOX_PULL(0)
+      LBM_FUSED_BOX_PULL(1)
+      LBM_FUSED_BOX_PULL(2)
+      LBM_FUSED_BOX_PULL(3)
+      LBM_FUSED_BOX_PULL(4)
+      LBM_FUSED_BOX_PULL(5)
+      LBM_FUSED_BOX_PULL(6)
+      LBM_FUSED_BOX_PULL(7)
+      LBM_FUSED_BOX_PULL(8)
+#undef LBM_FUSED_BOX_PULL
     } else {
 #define LBM_FUSED_WALL_PULL(I)                                     \
   {                                                                \
@@ -193,12 +244,12 @@ LBM_FORCEINLINE void fused_tile(const RunArgs& a, uint32_t txi, uint32_t tyi, ch
     R sc0 = (R)0, sc1 = (R)0, sr0 = (R)0, sr1 = (R)0;
     if constexpr (UK == 1) {
       if (tid < W0) {
-        const int32_t x = wrap_once(x0 + tid, nx);
+        // columns and rows beyond a wall are never collided; clamp to stay inside the table
+        const int32_t xx = grid_col(tid), x = WX ? (xx < 0 ? 0 : (xx >= nx ? nx - 1 : xx)) : xx;
         sc0 = tab[1 + x];
         sc1 = tab[tstride + 1 + x];
       }
       if (tid < H0) {
-        // rows beyond a wall are never collided; clamp to stay inside the table
         const int32_t yy = grid_row(tid), y = WY ? (yy < 0 ? 0 : (yy >= ny ? ny - 1 : yy)) : yy;
         sr0 = tab[1 + nx + y];
         sr1 = tab[tstride + 1 + nx + y];
@@ -210,8 +261,8 @@ LBM_FORCEINLINE void fused_tile(const RunArgs& a, uint32_t txi, uint32_t tyi, ch
       const int j = tid + k * NTH;
       if (K0 * NTH > C0 && j >= C0) return;
       const int ly = j / W0, lx = j - ly * W0;
-      const int32_t x = wrap_once(x0 + lx, nx), y = grid_row(ly);
-      if (outside(y)) return;
+      const int32_t x = grid_col(lx), y = grid_row(ly);
+      if (outside(x, y)) return;
       if constexpr (NP) {
         const uint32_t n = __umul24((uint32_t)y, (uint32_t)nx) + x, N = (uint32_t)nx * (uint32_t)ny;
         const char* np = (const char*)a.node_par;
@@ -219,7 +270,7 @@ LBM_FORCEINLINE void fused_tile(const RunArgs& a, uint32_t txi, uint32_t tyi, ch
         for (int c = 0; c < 3; ++c) npar[k][c] = gld<R>(np + (size_t)c * N * E, n * E);
       }
       const uint32_t xm = x == 0 ? nx - 1 : x - 1, xp = x + 1 == nx ? 0 : x + 1;
-      if (!WY || (y >= 1 && y < ny - 1)) {  // the plain pull (as in gather)
+      if (plain(x, y)) {
         const uint32_t r0 = __umul24((uint32_t)y, (uint32_t)nx), rm = y == 0 ? rlast : r0 - nx,
                        rp = y + 1 == ny ? 0u : r0 + nx;
         f[k][0] = gld<R>(spl[0], (r0 + x) * E);
@@ -231,6 +282,24 @@ LBM_FORCEINLINE void fused_tile(const RunArgs& a, uint32_t txi, uint32_t tyi, ch
         f[k][6] = gld<R>(spl[6], (rm + xp) * E);
         f[k][7] = gld<R>(spl[7], (rp + xp) * E);
         f[k][8] = gld<R>(spl[8], (rp + xm) * E);
+      } else if constexpr (WX) {
+#define LBM_FUSED_BOX_LOAD(I)                                                                   \
+  {                                                                                             \
+    int pop, dx, dy;                                                                            \
+    box_source<I>(a, x, y, nx, ny, pop, dx, dy);                                                \
+    const uint32_t so = (__umul24((uint32_t)(y + dy), (uint32_t)nx) + (uint32_t)(x + dx)) * E;  \
+    f[k][I] = gld<R>((const char*)a.src + (size_t)pop * pb, so);                                \
+  }
+        LBM_FUSED_BOX_LOAD(0)
+        LBM_FUSED_BOX_LOAD(1)
+        LBM_FUSED_BOX_LOAD(2)
+        LBM_FUSED_BOX_LOAD(3)
+        LBM_FUSED_BOX_LOAD(4)
+        LBM_FUSED_BOX_LOAD(5)
+        LBM_FUSED_BOX_LOAD(6)
+        LBM_FUSED_BOX_LOAD(7)
+        LBM_FUSED_BOX_LOAD(8)
+#undef LBM_FUSED_BOX_LOAD
       } else {
 #define LBM_FUSED_WALL_LOAD(I)                                                                  \
   {                                                                                             \
@@ -281,9 +350,9 @@ LBM_FORCEINLINE void fused_tile(const RunArgs& a, uint32_t txi, uint32_t tyi, ch
       const int j = tid + k * NTH;
       if (K0 * NTH > C0 && j >= C0) continue;
       const int ly = j / W0, lx = j - ly * W0;
-      const int32_t y = grid_row(ly);
-      if (outside(y)) continue;
-      collide(f[k], wrap_once(x0 + lx, nx), y, lx, ly, 0, npar[NP ? k : 0]);
+      const int32_t x = grid_col(lx), y = grid_row(ly);
+      if (outside(x, y)) continue;
+      collide(f[k], x, y, lx, ly, 0, npar[NP ? k : 0]);
 #pragma unroll
       for (int i = 0; i < 9; ++i) lds[i * C0 + j] = f[k][i];
       __builtin_amdgcn_sched_barrier(0);
@@ -312,19 +381,19 @@ LBM_FORCEINLINE void fused_tile(const RunArgs& a, uint32_t txi, uint32_t tyi, ch
       const int lx = slx[k], ly = sly[k];
       in[k] = (uint32_t)(lx - off) < (uint32_t)(W0 - 2 * off) && (uint32_t)(ly - off) < (uint32_t)(H0 - 2 * off);
       if (!in[k]) continue;
-      const int32_t y = grid_row(ly);
-      if (outside(y)) {
+      const int32_t x = grid_col(lx), y = grid_row(ly);
+      if (outside(x, y)) {
         in[k] = false;
         continue;
       }
-      gather(f[k], lx, ly, y);
+      gather(f[k], lx, ly, x, y);
     }
     __syncthreads();
 #pragma unroll
     for (int k = 0; k < K0; ++k) {
       if (!in[k]) continue;
       const int lx = slx[k], ly = sly[k];
-      collide(f[k], wrap_once(x0 + lx, nx), grid_row(ly), lx, ly, s - 1, npar[NP ? k : 0]);
+      collide(f[k], grid_col(lx), grid_row(ly), lx, ly, s - 1, npar[NP ? k : 0]);
 #pragma unroll
       for (int i = 0; i < 9; ++i) lds[i * C0 + ly * W0 + lx] = f[k][i];
     }
@@ -352,7 +421,7 @@ LBM_FORCEINLINE void fused_tile(const RunArgs& a, uint32_t txi, uint32_t tyi, ch
     const int32_t x = x0 + lx, y = y0 + ly;
     if (x >= nx || y >= ny) continue;
     R g[9];
-    gather(g, lx, ly, y);
+    gather(g, lx, ly, x, y);
     collide(g, x, y, lx, ly, T - 1, nullptr);
     if (VOUT && !store_end) continue;
     const uint32_t off = (__umul24((uint32_t)y, (uint32_t)nx) + x) * (uint32_t)sizeof(R);
@@ -361,14 +430,30 @@ LBM_FORCEINLINE void fused_tile(const RunArgs& a, uint32_t txi, uint32_t tyi, ch
   }
 }
 
+// The tile of a run with walls on both axes.
+// The compiler merges the wall rule with the plain pull, so that every node
+// pays for computing its sources; a tile whose widened nodes all lie off the
+// walls therefore takes the periodic form (2048^2 in 32 x 16 tiles: FP32 24.5
+// us a step, without it 26.4).  Grids of small tiles have few such tiles and
+// go without (16 x 16 at 256^2: 1.81 us, with it 2.12).
+template <typename R, int TX, int TY, int NTH, int T, int UK>
+LBM_FORCEINLINE void box_tile(const RunArgs& a, uint32_t txi, uint32_t tyi) {
+  const int32_t nx = (int32_t)a.nx, ny = (int32_t)a.ny, x1 = (int32_t)(txi * TX), y1 = (int32_t)(tyi * TY);
+  const bool off_x = x1 >= T && x1 + TX + T <= nx, off_y = y1 >= T && y1 + TY + T <= ny;
+  if (TX >= 32 && off_x && off_y) fused_tile<R, TX, TY, NTH, T, UK, false>(a, txi, tyi);
+  else fused_tile<R, TX, TY, NTH, T, UK, true, false, false, true>(a, txi, tyi);
+}
+
 // One run: one block per tile, in the chosen block order.  NP: the run has
 // per-node relaxation parameters (a D field; the branch is resolved at compile
 // time, so runs without them pay nothing for it).
-template <typename R, int BX, int BY, int NY, int T, int UK, bool WY, bool NP>
+template <typename R, int BX, int BY, int NY, int T, int UK, bool WY, bool NP, bool WX = false>
 __global__ __launch_bounds__(BX * BY) void k_fused_d2q9(const RunArgs a) {
   const uint32_t b = tile_of_block32(blockIdx.x, gridDim.x, a.tiles_x, a.xcd_remap);
   const uint32_t tyi = fdiv(b, a.tiles_x);
-  fused_tile<R, BX, tile_height(BY, NY), BX * BY, T, UK, WY, false, NP>(a, b - tyi * a.tiles_x.d, tyi);
+  constexpr int TY = tile_height(BY, NY);
+  if constexpr (WX) box_tile<R, BX, TY, BX * BY, T, UK>(a, b - tyi * a.tiles_x.d, tyi);
+  else fused_tile<R, BX, TY, BX * BY, T, UK, WY, false, NP>(a, b - tyi * a.tiles_x.d, tyi);
 }
 
 // The arguments of one step of a batched run (its compact record), for the

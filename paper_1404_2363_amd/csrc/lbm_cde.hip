@@ -792,6 +792,27 @@ const StepFn kSmallFn[2][kSmallCount] = {
     {launch_small<false, 0>, launch_small<false, 1>, launch_small<false, 2>, launch_small<false, 3>},
     {launch_small<true, 0>, launch_small<true, 1>, launch_small<true, 2>, launch_small<true, 3>}};
 
+template <bool DBL, int K>
+void launch_box(const RunArgs a, hipStream_t s) {
+  if (DBL) launch_box_f64(K, a, s);
+  else launch_box_f32(K, a, s);
+}
+const StepFn kBoxFn[2][kBoxCount] = {
+    {launch_box<false, 0>, launch_box<false, 1>}, {launch_box<true, 0>, launch_box<true, 1>}};
+
+Variant box_variant(int k) {
+  const SmallTile& t = kBox[k];
+  return Variant{t.bx, t.by, t.ny > 0 ? t.ny : 1, true, 1, 0, t.T};
+}
+
+// Walls on both axes: constant or separable velocity, constant D.
+bool box_ok(const Run& r) {
+  return r.d.lattice == LBM_CDE_D2Q9 && !r.half && r.d.bc[0] != LBM_CDE_PERIODIC &&
+         r.d.bc[1] != LBM_CDE_PERIODIC && r.d.nz == 1 &&
+         (r.d.model == LBM_CDE_MRT_A || r.d.model == LBM_CDE_MRT_B3) && r.d.u_kind != LBM_CDE_U_FIELD && !r.node_par &&
+         (double)r.nodes * (double)r.elem < 4294967296.0 && r.d.nx < (1ll << 24) && r.d.ny < (1ll << 24);
+}
+
 Variant small_variant(int k, int xcd = 1) {
   const SmallTile& t = kSmall[k];
   return Variant{t.bx, t.by, 1, true, xcd, 0, t.T};
@@ -843,6 +864,7 @@ const StepFn kStrip[2][kStripMax - 1] = {{launch_strip<false, 2>, launch_strip<f
 constexpr int64_t strip_nodes(bool dbl) { return dbl ? 300000 : 600000; }
 
 Variant small_start(const Run& r, const Variant& other) {
+  if (r.d.bc[0] != LBM_CDE_PERIODIC) return other;
   for (int k : {0, 1, 3, 2}) {
     const Variant v = small_variant(k);
     const int64_t tiles = (r.d.nx + v.bx - 1) / v.bx * ((r.d.ny + v.height() - 1) / v.height());
@@ -877,6 +899,19 @@ Variant tile_start(const Run& r) {
   const bool tall = r.dbl ? n24 == 1 && n8 >= 3 : 24 * n24 < 16 * n16 || (24 * n24 == 16 * n16 && !r.node_par);
   if (tall && find_step(r, kTile24)) return kTile24;
   return r.dbl ? kTile8 : kTile16;
+}
+
+// The tile that a run with walls on both axes starts with, four steps per launch.
+// Up to six tiles of 16 x 16 per CU those, a thread per node of the widened
+// tile, else 32 x 16.  Us a step in one-step launches, 16 x 16 and 32 x 16:
+// FP32 256^2 3.2, 1.8, 2.8; 600 x 480 7.4, 3.4, 3.8; 1000 x 900 16.7, 8.6,
+// 6.8; 2048^2 58, 36, 24; 4096 x 2500 127, 81, 53; FP64 600 x 480 12.2, 5.1,
+// 5.8; 1000 x 900 29.8, 11.6, 10.2; 2048^2 105, 50, 45; 4096 x 2500 247, 109,
+// 95.
+Variant box_start(const Run& r) {
+  const int64_t tiles16 = (r.d.nx + 15) / 16 * ((r.d.ny + 15) / 16);
+  const Variant v = box_variant(tiles16 <= 1536 ? 0 : 1);
+  return find_step(r, v) ? v : r.var;
 }
 
 Variant strip_start(const Run& r) {
@@ -937,6 +972,8 @@ StepFn find_step(const Run& r, const Variant& v) {
     return nullptr;
   }
   if (v.fuse != 1) {
+    for (int k = 0; k < kBoxCount; ++k)
+      if (v == box_variant(k) && box_ok(r)) return kBoxFn[p][k];
     if (v.fuse < 2 || !v.nt || !fused_ok(r, v)) return nullptr;
     for (const auto& e : kFused)
       if (e.bx == v.bx && e.by == v.by && e.ny == v.ny && e.T == v.fuse) return e.fn[p];
@@ -1508,7 +1545,7 @@ int init_runs(lbm_cde* h, const lbm_cde_run_desc* runs, int32_t nruns, const dou
       // runs that can take several steps per launch do so by default: large
       // ones by the marching kernel, the others in tiles
       if (r.d.lattice == LBM_CDE_D2Q9 && !r.half) {
-        const Variant tile = tile_start(r);
+        const Variant tile = r.d.bc[0] == LBM_CDE_PERIODIC ? tile_start(r) : box_start(r);
         if (find_step(r, tile)) r.var = small_start(r, tile);
         else r.var = small_start(r, r.var);
         // what an eight-step launch leaves over goes in 16 x 16 tiles
@@ -1887,8 +1924,11 @@ std::vector<Variant> run_candidates(const Run& r) {
       if (xcd == 1 && vol_ok(r))
         for (int k = 0; k < 2; ++k) add(vol_variant(r, k));
     } else {
-      for (int k = 0; k < kSmallCount; ++k)
-        if (xcd == 1 && find_step(r, small_variant(k))) add(small_variant(k));
+      const bool box = r.d.bc[0] != LBM_CDE_PERIODIC;
+      for (int k = 0; xcd == 1 && k < (box ? kBoxCount : kSmallCount); ++k) {
+        const Variant c = box ? box_variant(k) : small_variant(k);
+        if (find_step(r, c)) add(c);
+      }
       for (const auto& e : kSteps) add(Variant{e.bx, e.by, e.ny, e.nt, xcd});
       for (const auto& e : kFused) {
         const Variant c{e.bx, e.by, e.ny, true, xcd, 0, e.T};
