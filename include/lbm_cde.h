@@ -279,7 +279,9 @@ int lbm_cde_set_velocity(lbm_cde_handle h, int32_t run, const double* u);
  * steps left over when a call's count is not a multiple go one per launch.
  * Grids of up to 512 x 512 nodes have launches of their own: 8 x 64, 16 x 64
  * and 32 x 32 threads that take 8 steps of an 8 x 8, 16 x 16 or 32 x 32 tile,
- * and 16 x 32 threads that take 4 of a 16 x 16 tile.  Blocks of 64 x 1 name
+ * and 16 x 32 threads that take 4 of a 16 x 16 tile.  Runs of constant D and
+ * constant or separable velocity with walls on both axes take 4 steps of a
+ * 16 x 16 (16 x 32 threads) or 32 x 16 tile.  Blocks of 64 x 1 name
  * the launches whose waves march along y with the steps between in
  * registers, 4 to 6 at a time: for such runs with a
  * constant D and a constant or separable velocity (factor 1 in z) at least 64
@@ -288,12 +290,12 @@ int lbm_cde_set_velocity(lbm_cde_handle h, int32_t run, const double* u);
  * D3Q15 runs with a constant or separable velocity, periodic or mirrored in x
  * and y (any kind in z), take two steps per launch over blocks of columns that
  * march along z, and start so.
- * A run that can take several steps per launch starts with 4 (64 x 24
- * tiles in FP32 where the grid allows them, else 64 x 16; 64 x 8 in FP64),
- * one of at most 256 small tiles with the launch of the smallest such tile (4
- * steps with walls and between 16,384 and 49,152 nodes, else 8), one of
- * 600,000 nodes or more (300,000 in FP64) that can march, and a batch of as
- * many, with a marching launch of 4 to 6; any other with one.  A batched handle has
+ * A run that can take several steps per launch starts with 4 (tiles of 64
+ * columns and 24, 16 or, in FP64, 8 rows, by the tiles on the fullest CU), one
+ * of at most 256 small tiles with the launch of the smallest such tile (4 steps
+ * between 16,384 and 49,152 nodes and, for up to 512 tiles, with walls; else
+ * 8), one of 600,000 nodes or more (300,000 in FP64) that can march, and a
+ * batch of 100,000, with a marching launch of 4 to 6; any other with one.  A batched handle has
  * one variant for all its runs; the run index only has to be valid.  Results
  * are bitwise the same for every variant. */
 
