@@ -97,6 +97,7 @@ struct RunArgs {
   int32_t active;           // 0: run has used its step budget
   int64_t max_steps;        // step budget (< 0: unlimited), used by batched launches
   double xref0, xref_drift; // sampled x-moments: x_ref(t) = xref0 + xref_drift * t
+  int32_t cut[3];           // two D3Q15 steps per launch: columns and planes of a block (vol_cut)
 };
 
 // Block id remapping for the 8 XCDs of MI355X: consecutive hardware block ids

@@ -1,6 +1,6 @@
 // Two D3Q15 steps per launch: blocks that march along z.
 //
-// A block owns TX x TY columns of nodes and walks the planes of its chunk.
+// A block owns a tile of columns of nodes and walks the planes of its chunk.
 // At plane p it pulls the stored state of the columns widened by one node on
 // every side (one node per thread), does the first step and publishes the
 // result in LDS; the threads of the block's own columns gather from there what
@@ -53,23 +53,31 @@ LBM_FORCEINLINE void lds_barrier() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
-// n planes from z0 on; block of NTH >= (TX + 2)(TY + 2) threads.  WXY: a wall
-// in x or y (every byte offset in the Q planes then fits 32 bits, else those
-// in a plane z = const); WZ: walls in z.
+// j / w for 0 <= j < 1024 and 1 <= w <= 66: the quotient is at least 1 / 132 off
+// an integer, the reciprocal's error at most 1e-4 of it.
+LBM_FORCEINLINE int row_of(int j, int w) { return (int)(((float)j + 0.5f) * __builtin_amdgcn_rcpf((float)w)); }
+
+// A chunk of cut[2] planes of a tile of cut[0] x cut[1] columns: TX x TY, or
+// fewer on grids that are narrower or have too few tiles (vol_cut); a block has
+// a thread for every widened column, at most NTH.  WXY: a wall in x or y (every
+// byte offset in the Q planes then fits 32 bits, else those in a plane z =
+// const); WZ: walls in z.
 template <typename R, int TX, int TY, int NTH, int UK, bool WXY, bool WZ>
-__global__ __launch_bounds__(NTH) void k_fused_d3q15(const RunArgs a, int32_t L) {
-  constexpr int W0 = TX + 2, H0 = TY + 2, C0 = W0 * H0;
+__global__ __launch_bounds__(NTH) void k_fused_d3q15(const RunArgs a) {
+  constexpr int W0 = TX + 2, C0 = W0 * (TY + 2);  // the LDS keeps the full tile's pitch
+  const int32_t tx = a.cut[0], ty = a.cut[1], L = a.cut[2];
   // planes a pull is ahead of its use; with walls in the plane and across it
   // the registers of a second one would spill
   constexpr int PF = WXY && WZ ? 1 : 2;
-  static_assert(NTH >= C0 && NTH >= TX * TY, "one node per thread");
+  static_assert(NTH >= C0, "one node per thread");
   constexpr uint32_t E = sizeof(R);
   __shared__ R lds[15 * C0];
   const int tid = threadIdx.x;
   const int32_t nx = (int32_t)a.nx, ny = (int32_t)a.ny, nz = (int32_t)a.nz;
   const uint32_t b = tile_of_block32(blockIdx.x, gridDim.x, a.tiles_x, 1);
   const uint32_t rest = fdiv(b, a.tiles_x), cz = fdiv(rest, a.tiles_y);
-  const int32_t x0 = (int32_t)(b - rest * a.tiles_x.d) * TX, y0 = (int32_t)(rest - cz * a.tiles_y.d) * TY;
+  const int32_t x0 = (int32_t)(b - rest * a.tiles_x.d) * tx, y0 = (int32_t)(rest - cz * a.tiles_y.d) * ty;
+  const int32_t w0 = tx + 2, nown = tx * ty, nwide = w0 * (ty + 2);
   const int32_t z0 = __builtin_amdgcn_readfirstlane((int32_t)cz * L);
   const int32_t z1 = __builtin_amdgcn_readfirstlane(min(z0 + L, nz));
   const size_t pb = (size_t)a.plane * E, sz = (size_t)nx * (size_t)ny * E;
@@ -81,15 +89,15 @@ __global__ __launch_bounds__(NTH) void k_fused_d3q15(const RunArgs a, int32_t L)
   // the thread's node of the widened columns (first step).  Columns beyond a
   // wall or past the far edge of the last tile (+ its halo) are not needed;
   // they are clamped to valid addresses.
-  const int jl = min(tid, C0 - 1), ly1 = jl / W0, lx1 = jl - ly1 * W0;
+  const int jl = min(tid, nwide - 1), ly1 = row_of(jl, w0), lx1 = jl - ly1 * w0, j1 = ly1 * W0 + lx1;
   auto wrap = [](int32_t v, int32_t n, bool per) {
     return per ? (v < 0 ? v + n : (v >= n ? v - n : v)) : (v < 0 ? 0 : (v >= n ? n - 1 : v));
   };
   const int32_t xa = wrap(min(x0 + lx1 - 1, nx), nx, px), ya = wrap(min(y0 + ly1 - 1, ny), ny, py);
   // and of the block's own columns (second step)
-  const int lx2 = tid % TX, ly2 = tid / TX;
+  const int jo = min(tid, nown - 1), ly2 = row_of(jo, tx), lx2 = jo - ly2 * tx;
   const int32_t xb = min(x0 + lx2, nx - 1), yb = min(y0 + ly2, ny - 1);
-  const bool own = tid < TX * TY && x0 + lx2 < nx && y0 + ly2 < ny;
+  const bool wide = tid < nwide, mine = tid < nown, own = mine && x0 + lx2 < nx && y0 + ly2 < ny;
 
   // static byte offset of population i's pull within a plane of nodes, the
   // population plane included.  A mirror wall in x or y reverses that
@@ -110,7 +118,7 @@ __global__ __launch_bounds__(NTH) void k_fused_d3q15(const RunArgs a, int32_t L)
   }
   // where the second step finds population i of its node in LDS
   int at[15];
-  const int j2 = (min(ly2, TY - 1) + 1) * W0 + lx2 + 1;
+  const int j2 = (ly2 + 1) * W0 + lx2 + 1;
 #pragma unroll
   for (int i = 0; i < 15; ++i) {
     int pop = i, dx = -kEx15[i], dy = -kEy15[i];
@@ -225,7 +233,7 @@ __global__ __launch_bounds__(NTH) void k_fused_d3q15(const RunArgs a, int32_t L)
   };
   auto plane = [&](R(&f)[15], R(&nf)[15]) {
     const int32_t z = image(p);
-    if (tid < C0) {
+    if (wide) {
       R w[3];
       if constexpr (UK == 1) {
 #pragma unroll
@@ -233,12 +241,12 @@ __global__ __launch_bounds__(NTH) void k_fused_d3q15(const RunArgs a, int32_t L)
       }
       collide(f, va, w);
 #pragma unroll
-      for (int i = 0; i < 15; ++i) lds[i * C0 + tid] = f[i];
+      for (int i = 0; i < 15; ++i) lds[i * C0 + j1] = f[i];
     }
     load(f, image(min(p + PF, plast)));
     lds_barrier();
     R dn[5], nu[5], nm[5];
-    if (tid < TX * TY) {
+    if (mine) {
 #pragma unroll
       for (int k = 0; k < 5; ++k) {
         dn[k] = lds[at[kDown15[k]]];
@@ -257,7 +265,7 @@ __global__ __launch_bounds__(NTH) void k_fused_d3q15(const RunArgs a, int32_t L)
       }
     }
     lds_barrier();
-    if (tid < TX * TY) {
+    if (mine) {
       if (p > z0) second(p - 1, dn, nf);
 #pragma unroll
       for (int k = 0; k < 5; ++k) {
@@ -277,7 +285,7 @@ __global__ __launch_bounds__(NTH) void k_fused_d3q15(const RunArgs a, int32_t L)
     }
     if (p <= plast) plane(fa, fb);
   }
-  if (WZ && z1 == nz && tid < TX * TY) second(nz - 1, top, fa);  // no plane above the last one
+  if (WZ && z1 == nz && mine) second(nz - 1, top, fa);  // no plane above the last one
 }
 
 }  // namespace lbm

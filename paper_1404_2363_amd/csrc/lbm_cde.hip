@@ -120,6 +120,7 @@ struct Run {
   int64_t steps = 0;
   int cur = 0;         // population buffer (0/1) that holds the current state
   bool walls = false;
+  VolCut vol[2] = {};  // D3Q15, two steps per launch: the cut over each of kVolTiles
   Variant var{256, 1, 1, true, false};
   Variant var4{256, 1, 1, true, false};  // four-step launches for what an eight-step variant leaves over
   Variant var1{256, 1, 1, true, false};  // one-step launches (the steps a multi-step variant leaves over)
@@ -607,6 +608,12 @@ RunArgs make_args(const lbm_cde* h, const Run& r, int parity, const Variant* lau
              (double)r.plane * r.Q * r.elem < 4294967296.0 && r.d.nx < (1ll << 31) && r.d.ny < (1ll << 31) &&
              (r.d.u_kind != LBM_CDE_U_FIELD || 16.0 * (double)r.nodes < 4294967296.0);
   if (a.xcd_remap == 2 && tile_rows(r, var) % 8 != 0) a.xcd_remap = 0;
+  if (r.d.lattice == LBM_CDE_D3Q15 && var.fuse == 2) {
+    const VolCut& c = r.vol[var.bx == kVolTiles[r.dbl][0][0] && var.by == kVolTiles[r.dbl][0][1] ? 0 : 1];
+    a.cut[0] = c.tx;
+    a.cut[1] = c.ty;
+    a.cut[2] = c.L;
+  }
   a.active = 1;
   return a;
 }
@@ -954,13 +961,8 @@ Variant vol_variant(const Run& r, int k) {
 
 // The tile of the two that should be faster, or the one-step launch.
 Variant vol_start(const Run& r, const Variant& one) {
-  if (!vol_ok(r)) return one;
-  double cost[2];
-  for (int k = 0; k < 2; ++k) {
-    const auto& t = kVolTiles[r.dbl ? 1 : 0][k];
-    cost[k] = vol_cut(t[0], t[1], r.dbl, r.d.nx, r.d.ny, r.d.nz).cost;
-  }
-  return vol_variant(r, cost[1] < cost[0] ? 1 : 0);
+  if (!vol_ok(r) || vol_one_step(r.walls, r.dbl, r.d.nx, r.d.ny, r.d.nz)) return one;
+  return vol_variant(r, r.vol[1].cost < r.vol[0].cost ? 1 : 0);
 }
 
 StepFn find_step(const Run& r, const Variant& v) {
@@ -1553,7 +1555,15 @@ int init_runs(lbm_cde* h, const lbm_cde_run_desc* runs, int32_t nruns, const dou
       }
       const Variant march = strip_start(r);
       if (march.fuse > 1) r.var = march;
-      else if (r.d.lattice == LBM_CDE_D3Q15) r.var = vol_start(r, r.var);
+      if (r.d.lattice == LBM_CDE_D3Q15) {
+        const bool wz =
+            r.d.bc[2] != LBM_CDE_PERIODIC && r.d.bc[0] == LBM_CDE_PERIODIC && r.d.bc[1] == LBM_CDE_PERIODIC;
+        for (int k = 0; k < 2; ++k) {
+          const auto& t = kVolTiles[r.dbl][k];
+          r.vol[k] = vol_cut(t[0], t[1], r.dbl, wz, r.d.nx, r.d.ny, r.d.nz);
+        }
+        r.var = vol_start(r, r.var);
+      }
     }
     if (r.split && h->env16_set) r.var = h->env16;
     if (h->env_variant && !r.half) r.var = r.d.lattice == LBM_CDE_D3Q15 ? h->env3 : h->env;
