@@ -889,9 +889,12 @@ Variant small_start(const Run& r, const Variant& other) {
 // tiles: with t tiles that is ceil(t / 256), each a time of about its rows.
 // FP32, us a step in 64 x 24 and 64 x 16 tiles: 600 x 480 2.45 and 2.82 (1 and
 // 2 tiles on the fullest CU), 700 x 600 3.66 and 3.13 (2 and 2), 760^2 4.02
-// and 4.81 (2 and 3), 300^2 between walls 2.57 and 2.36 (1 and 1).  A D field
-// needs registers that 768 threads do not have: equal rows go to 64 x 16
-// (1500 x 1400 17.2 and 13.5).  FP64 takes the 64 x 24 tile, whose LDS fills a
+// and 4.81 (2 and 3), 300^2 between walls 2.57 and 2.36 (1 and 1).  From three on
+// the last round weighs less than the smaller halo of 64 x 24, unless a grid of
+// few rows has no fewer of them (velocity field: 1024^2 7.9 and 8.4, 2048^2 25.7
+// and 29.7, 4096^2 115 and 141; 1536 x 512, 3 and 3, 7.7 and 6.6).  A D field
+// needs registers that 768 threads do not have: more than one tile per CU go to
+// 64 x 16 (1100 x 1000 8.9 and 7.8, 1500 x 1400 17.2 and 13.5).  FP64 takes the 64 x 24 tile, whose LDS fills a
 // CU, where one per CU is enough and there would be three or more of 64 x 8:
 // 600 x 480 4.19 and 4.84, 2000 x 150 between walls 4.45 and 5.74 (marching
 // 5.46), 640 x 480 4.25 and 4.93 (marching 4.37); 700 x 600 7.70 and 6.03.
@@ -903,7 +906,9 @@ int64_t tiles_per_cu(const Run& r, const Variant& v) {
 
 Variant tile_start(const Run& r) {
   const int64_t n24 = tiles_per_cu(r, kTile24), n16 = tiles_per_cu(r, kTile16), n8 = tiles_per_cu(r, kTile8);
-  const bool tall = r.dbl ? n24 == 1 && n8 >= 3 : 24 * n24 < 16 * n16 || (24 * n24 == 16 * n16 && !r.node_par);
+  const bool tall = r.dbl        ? n24 == 1 && n8 >= 3
+                    : r.node_par ? n24 == 1 && n16 >= 2
+                                 : 24 * n24 <= 16 * n16 || (n24 >= 3 && n16 > n24);
   if (tall && find_step(r, kTile24)) return kTile24;
   return r.dbl ? kTile8 : kTile16;
 }

@@ -11,7 +11,7 @@ from paper_1404_2363_amd import workloads as W
 
 pytestmark = pytest.mark.gpu
 
-T24, T8 = (64, 12, 2), (64, 4, 2)  # four steps of 64 x 24 and 64 x 8 tiles
+T24, T16, T8 = (64, 12, 2), (64, 8, 2), (64, 4, 2)  # four steps of 64 x 24, 64 x 16 and 64 x 8 tiles
 
 
 def _workload(nx, ny, kind):
@@ -20,6 +20,8 @@ def _workload(nx, ny, kind):
         rng = W.rng_for(97, nx)
         return dataclasses.replace(wl, D=None, D_field=W.dfield_from(*(W.fourier_field(rng, nx, ny, kmax=2)
                                                                        for _ in range(3)))), {"heat": [1.0, 1.1]}
+    if kind == "field":
+        return dataclasses.replace(wl, u_field=wl.u(), u_sep=None), {}
     return wl, {}
 
 
@@ -39,7 +41,8 @@ def _best(runs, n=96, tries=7):
 
 @pytest.mark.parametrize("precision,nx,ny,kind,tile", [
     ("fp64", 300, 300, "periodic", T8), ("fp64", 300, 290, "dfield", T8), ("fp64", 257, 256, "dfield", T8),
-    ("fp64", 1000, 100, "dfield", T8),
+    ("fp64", 1000, 100, "dfield", T8), ("fp32", 2048, 2048, "field", T24), ("fp32", 1200, 1000, "field", T24),
+    ("fp32", 1100, 1000, "dfield", T16),
 ])
 def test_start_is_not_slower_than_tiles(precision, nx, ny, kind, tile):
     from paper_1404_2363_amd.solver import Solver
