@@ -863,11 +863,13 @@ const StepFn kStrip[2][kStripMax - 1] = {{launch_strip<false, 2>, launch_strip<f
 
 // The marching launch that a run starts with (fuse 1: none): large grids whose
 // width fills the strips.  On smaller grids the waves of a launch have few rows
-// each and the halo rows dominate.  FP32: 3007 x 127 between walls 4.65 us a
-// step against 4.05 in LDS tiles, 724^2 3.8 against 3.9, 3000 x 301 5.5
-// against 6.0, 1024^2 5.6 against 6.2; FP64: 512^2 3.4 against 2.9, 724^2 4.8
-// against 7.8.  A strip that keeps less than 70 % of its lanes costs more than
-// the tiles' halo.
+// each and the halo rows dominate.  FP64, us a step against the tiles: 512^2
+// 3.4 and 2.9, 724^2 4.8 and 7.8.  FP32 from three 64 x 24 tiles on the fullest CU
+// on: 850^2 (2) 4.7 and 4.1, 870^2 (3) 4.7 and 5.5, 1024^2 (3) 5.6 and 6.2; between
+// walls, where the ends of every chunk cost more, from five on: 870^2 (3) 6.1 and
+// 6.3, 1024^2 (3) 7.2 and 6.7, 1200^2 (4) 8.2 and 7.8, 1250^2 (5) 8.7 and 10.4,
+// 20000 x 64 (4) 8.1 and 7.7.  A strip that keeps less than 70 % of its lanes
+// costs more than the tiles' halo.
 constexpr int64_t strip_nodes(bool dbl) { return dbl ? 300000 : 600000; }
 
 Variant small_start(const Run& r, const Variant& other) {
@@ -927,12 +929,14 @@ Variant box_start(const Run& r) {
 }
 
 Variant strip_start(const Run& r) {
+  const bool walls = r.d.bc[1] != LBM_CDE_PERIODIC;
   if (r.dbl && tile_start(r) == kTile24) return strip_variant(1);
+  if (!r.dbl && find_step(r, kTile24) && tiles_per_cu(r, kTile24) < (walls ? 5 : 3)) return strip_variant(1);
   StripCut best{1, 0, 1e300};
   for (int T = 4; T <= kStripMax; ++T) {
     const int64_t nsx = (r.d.nx + strip_width(T) - 1) / strip_width(T);
     if (!strip_ok(r, T) || r.nodes < strip_nodes(r.dbl) || 10 * r.d.nx < 7 * 64 * nsx) continue;
-    const StripCut c = strip_cut_run(T, r.d.nx, r.d.ny, r.dbl);
+    const StripCut c = strip_cut_run(T, r.d.nx, r.d.ny, r.dbl, walls);
     if (c.cost < best.cost) best = c;
   }
   return strip_variant(best.T);
@@ -1440,7 +1444,7 @@ std::vector<Variant> batch_fused_candidates(const lbm_cde* h) {
 StripCut strip_cut_batch(const lbm_cde* h, int T) {
   int64_t tall = 1;
   for (const Run& r : h->runs) tall = std::max<int64_t>(tall, r.d.ny);
-  return strip_cut(T, tall, h->runs[0].dbl, [&](auto f) {
+  return strip_cut(T, tall, h->runs[0].dbl, h->runs[0].d.bc[1] != LBM_CDE_PERIODIC, [&](auto f) {
     for (const Run& r : h->runs) f(r.d.ny, (r.d.nx + strip_width(T) - 1) / strip_width(T));
   });
 }

@@ -20,6 +20,10 @@ def _workload(nx, ny, kind):
         rng = W.rng_for(97, nx)
         return dataclasses.replace(wl, D=None, D_field=W.dfield_from(*(W.fourier_field(rng, nx, ny, kmax=2)
                                                                        for _ in range(3)))), {"heat": [1.0, 1.1]}
+    if kind == "walls":
+        one, prof = np.ones(1), np.sin(np.pi * (np.arange(ny) + 0.5) / ny)
+        return dataclasses.replace(wl, walls=("periodic", "bounce"), D=0.08 * np.eye(2), u_sep=W.SeparableU(
+            np.array([0.05, 0.0]), [[np.ones(nx), prof, one], [np.ones(nx), np.zeros(ny), one]])), {}
     if kind == "field":
         return dataclasses.replace(wl, u_field=wl.u(), u_sep=None), {}
     return wl, {}
@@ -42,7 +46,9 @@ def _best(runs, n=96, tries=7):
 @pytest.mark.parametrize("precision,nx,ny,kind,tile", [
     ("fp64", 300, 300, "periodic", T8), ("fp64", 300, 290, "dfield", T8), ("fp64", 257, 256, "dfield", T8),
     ("fp64", 1000, 100, "dfield", T8), ("fp32", 2048, 2048, "field", T24), ("fp32", 1200, 1000, "field", T24),
-    ("fp32", 1100, 1000, "dfield", T16),
+    ("fp32", 1100, 1000, "dfield", T16), ("fp32", 830, 830, "periodic", T24), ("fp32", 870, 870, "periodic", T24),
+    ("fp32", 830, 830, "walls", T24), ("fp32", 1024, 1024, "walls", T24), ("fp32", 1200, 1200, "walls", T24),
+    ("fp32", 1250, 1250, "walls", T24), ("fp32", 900, 2400, "walls", T24),
 ])
 def test_start_is_not_slower_than_tiles(precision, nx, ny, kind, tile):
     from paper_1404_2363_amd.solver import Solver
