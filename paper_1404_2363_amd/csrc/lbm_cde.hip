@@ -1449,8 +1449,46 @@ StripCut strip_cut_batch(const lbm_cde* h, int T) {
   });
 }
 
+// How much longer the marching launches of cut c take over the batch's steps than
+// they would if their time fell with the nodes still active: the cut stays that
+// of all runs, so where it only just fills the SIMDs a launch takes as long after
+// half of the runs have ended.  With unlimited runs only these count.
+double batch_strip_loss(const lbm_cde* h, const StripCut& c) {
+  const auto& order = h->batch_order;  // by decreasing budget, unlimited first
+  auto run = [&](size_t i) -> const Run& { return h->runs[order[i]]; };
+  auto cost = [&](size_t active) {
+    return strip_cost(c.T, c.L, h->runs[0].dbl, 1.0, [&](auto f) {
+      for (size_t i = 0; i < active; ++i) f(run(i).d.ny, (run(i).d.nx + strip_width(c.T) - 1) / strip_width(c.T));
+    });
+  };
+  double all = 0.0, nodes = 0.0, spent = 0.0, fair = 0.0;
+  for (const Run& r : h->runs) all += (double)r.nodes;
+  const double full = cost(order.size());
+  for (size_t i = 0; i < order.size(); ++i) {  // runs 0 .. i are active up to the budget of run i
+    nodes += (double)run(i).nodes;
+    const int64_t end = run(i).d.max_steps, next = i + 1 < order.size() ? run(i + 1).d.max_steps : 0;
+    if (end < 0 && next < 0) continue;
+    const double steps = end < 0 ? 1.0 : (double)(end - next);
+    spent += steps * cost(i + 1);
+    fair += steps * full * nodes / all;
+    if (end < 0) break;
+  }
+  return fair > 0.0 ? spent / fair : 1.0;
+}
+
 // The marching launch that a batch starts with (fuse 1: none; see strip_start).
-Variant batch_strip_start(const lbm_cde* h) {
+// A batch that could take tiles (`tiles`) marches up to the loss at which these,
+// which need fewer rounds as runs end, catch up: FP64 1.75, FP32 1.36, between
+// walls in FP32 and below 4,000,000 nodes, where the march leads by little, 1.1.
+// 910 steps, march and tiles, ms: FP64 three 700^2, all runs 9.1 and 14.8, one
+// ending early (loss 1.5) 7.9 and 11.0, two (3.0) 7.7 and 6.2; two 512^2, one
+// ending early (2.0) 5.3 and 3.8.  FP32 four 512^2, one ending early (1.34) 5.2
+// and 5.7, two (1.38) 4.3 and 3.9; between walls six channels of 4096 x 64 .. 104,
+// one ending early (1.14) 11.0 and 9.3, 64 channels, half of them ending early
+// (1.18) 27 and 32.
+Variant batch_strip_start(const lbm_cde* h, bool tiles) {
+  const Run& r0 = h->runs[0];
+  const bool walls = r0.d.bc[1] != LBM_CDE_PERIODIC;
   int64_t nodes = 0;
   for (const Run& r : h->runs) nodes += r.nodes;
   StripCut best{1, 0, 1e300};
@@ -1460,11 +1498,12 @@ Variant batch_strip_start(const lbm_cde* h) {
       lanes += (r.d.nx + strip_width(T) - 1) / strip_width(T) * 64;
       kept += r.d.nx;
     }
-    if (nodes < strip_nodes(h->runs[0].dbl) || 10 * kept < 7 * lanes || !find_batch_fused(h, strip_variant(T))) continue;
+    if (nodes < strip_nodes(r0.dbl) || 10 * kept < 7 * lanes || !find_batch_fused(h, strip_variant(T))) continue;
     const StripCut c = strip_cut_batch(h, T);
     if (c.cost < best.cost) best = c;
   }
-  return strip_variant(best.T);
+  const double limit = r0.dbl ? 1.75 : walls && nodes < 4000000 ? 1.1 : 1.36;
+  return strip_variant(best.T > 1 && (!tiles || batch_strip_loss(h, best) <= limit) ? best.T : 1);
 }
 
 // Make v the multi-step batched launch (v.fuse > 1; validated by the caller
@@ -1700,7 +1739,7 @@ int init_runs(lbm_cde* h, const lbm_cde_run_desc* runs, int32_t nruns, const dou
     // "BXxBYxNYxT" fixes the multi-step one
     Variant fv = h->runs[0].dbl ? Variant{64, 4, 2, true, 0, 0, 4} : Variant{64, 12, 2, true, 0, 0, 4};
     if (!find_batch_fused(h, fv)) fv = Variant{64, 8, 2, true, 0, 0, 4};
-    const Variant march = batch_strip_start(h);
+    const Variant march = batch_strip_start(h, find_batch_fused(h, fv) != nullptr);
     if (march.fuse > 1) fv = march;
     int fbx, fby, fny, ft;
     if (const char* e = std::getenv("LBM_CDE_BATCH_FUSE"))

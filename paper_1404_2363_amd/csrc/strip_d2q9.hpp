@@ -312,17 +312,34 @@ struct StripCut {
   double cost;  // time per step, in units of one step of a row on one SIMD
 };
 
-// rows(f) calls f(height, strips) for every run.  Between walls the rows at a
-// chunk's ends, which test every step, take about three times as long in FP32
-// (1024^2, T = 4, 5, 6: 5.5, 5.6 and 5.8 us a step periodic, 7.2, 7.6 and 8.1
-// between walls).  The cost says so, and fewer steps per launch win on smaller
-// grids; the chunks stay those of the periodic march, since longer ones leave
-// SIMDs idle (870^2 T = 4 6.1 us a step, in chunks by that cost 6.3).
+// The cost of a launch with chunks of L rows; rows(f) calls f(height, strips) for
+// every run, a chunk's ends cost `ends` times their T - 1 rows.
+template <typename Rows>
+double strip_cost(int T, int64_t L, bool dbl, double ends, Rows rows) {
+  const double two = dbl ? 1.84 : 1.55, fixed = dbl ? 15.0 : 19.0, h = ends * (double)(T - 1);
+  double all = 0.0, chunks = 0.0;
+  int64_t least = L;
+  rows([&](int64_t ny, int64_t strips) {
+    const int64_t n = (ny + L - 1) / L;
+    all += (double)strips * (double)ny;
+    chunks += (double)(strips * n);
+    least = std::min(least, (ny + n - 1) / n);
+  });
+  const double x = chunks / 1024.0, k = std::ceil(x);
+  const double last = (all + chunks * h) / 1024.0 + (k - x) * ((double)least + h);
+  return (last * (k >= 2.0 ? 0.5 * two : 1.0) * (T + 2.5) + fixed) / T;
+}
+
+// Between walls the rows at a chunk's ends, which test every step, take about
+// three times as long in FP32 (1024^2, T = 4, 5, 6: 5.5, 5.6 and 5.8 us a step
+// periodic, 7.2, 7.6 and 8.1 between walls).  The cost says so, and fewer steps
+// per launch win on smaller grids; the chunks stay those of the periodic march,
+// since longer ones leave SIMDs idle (870^2 T = 4 6.1 us a step, in chunks by that
+// cost 6.3).
 template <typename Rows>
 StripCut strip_cut(int T, int64_t ny_max, bool dbl, bool walls, Rows rows) {
-  const double two = dbl ? 1.84 : 1.55, fixed = dbl ? 15.0 : 19.0, ends = walls && !dbl ? 3.0 : 1.0;
   StripCut best{T, 0, 1e300};
-  double least_cost = 1e300, strips_all = 0.0;
+  double strips_all = 0.0;
   rows([&](int64_t, int64_t strips) { strips_all += (double)strips; });
   // whole columns and a few chunks of them, and the cuts that just fill the
   // SIMDs once and twice (three times: more row streams than the memory likes,
@@ -331,25 +348,10 @@ StripCut strip_cut(int T, int64_t ny_max, bool dbl, bool walls, Rows rows) {
     const int64_t nc = c <= 4 ? c : (int64_t)((c - 4) * 1024.0 / strips_all);
     if (nc < 1 || (nc > 1 && ny_max / nc < 2)) continue;
     const int64_t L = (ny_max + nc - 1) / nc;
-    double all = 0.0, chunks = 0.0;
-    int64_t least = L;
-    rows([&](int64_t ny, int64_t strips) {
-      const int64_t n = (ny + L - 1) / L;
-      all += (double)strips * (double)ny;
-      chunks += (double)(strips * n);
-      least = std::min(least, (ny + n - 1) / n);
-    });
-    const double x = chunks / 1024.0, k = std::ceil(x);
-    auto cost = [&](double e) {  // e: rows' work of the T - 1 at a chunk's ends
-      const double h = e * (double)(T - 1);
-      const double last = (all + chunks * h) / 1024.0 + (k - x) * ((double)least + h);
-      return (last * (k >= 2.0 ? 0.5 * two : 1.0) * (T + 2.5) + fixed) / T;
-    };
-    if (cost(1.0) < least_cost) {
-      least_cost = cost(1.0);
-      best = StripCut{T, (int32_t)L, cost(ends)};
-    }
+    const double cost = strip_cost(T, L, dbl, 1.0, rows);
+    if (cost < best.cost) best = StripCut{T, (int32_t)L, cost};
   }
+  if (walls && !dbl) best.cost = strip_cost(T, best.L, dbl, 3.0, rows);
   return best;
 }
 

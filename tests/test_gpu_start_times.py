@@ -61,3 +61,30 @@ def test_start_is_not_slower_than_tiles(precision, nx, ny, kind, tile):
     for s in runs:
         s.close()
     assert start <= 1.05 * tiles
+
+
+@pytest.mark.parametrize("precision,nx,ny,nruns,ending,marches", [
+    ("fp64", 512, 512, 2, 1, False), ("fp64", 700, 700, 3, 2, False), ("fp64", 700, 700, 3, 1, True),
+    ("fp64", 512, 512, 2, 0, True), ("fp32", 512, 512, 4, 2, False), ("fp32", 512, 512, 4, 0, True),
+])
+def test_batch_whose_runs_end(precision, nx, ny, nruns, ending, marches):
+    """A batch marches while its runs fill the cut made for all of them: with
+    runs that end early it starts with tiles, and is no slower than those."""
+    import torch
+    from paper_1404_2363_amd.solver import Solver
+    wl, _ = _workload(nx, ny, "periodic")
+    per = [{"max_steps": 20 if i < ending else -1} for i in range(nruns)]
+    runs = [Solver([wl] * nruns, precision, per_run=per) for _ in range(2)]
+    assert (runs[0].variant()["block"] == (64, 1)) == marches
+    bx, by, ny_ = T8 if precision == "fp64" else T24
+    runs[1].set_variant({"block": (bx, by), "rows_per_thread": ny_, "nt_stores": True, "block_order": 0, "grid": 0,
+                         "steps_per_launch": 4})
+    for s in runs:
+        s.step(20)
+    torch.cuda.synchronize()
+    start, tiles = _best(runs)
+    print(f"case batch {nruns} x {nx}x{ny} {precision}, {ending} end: {start * 1e6:.0f} us, tiles {tiles * 1e6:.0f} us",
+          flush=True)
+    for s in runs:
+        s.close()
+    assert start <= 1.05 * tiles
