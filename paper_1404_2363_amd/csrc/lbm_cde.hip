@@ -30,6 +30,7 @@
 #include "fp16_d2q9.hpp"
 #include "fused_d2q9.hpp"
 #include "fused_launch.hpp"
+#include "batch_block.hpp"
 #include "adjoint_fused_d2q9.hpp"
 #include "stability.hpp"
 #include "strip_d2q9.hpp"
@@ -1558,10 +1559,16 @@ unsigned batch_fgrid_at(const lbm_cde* h, int64_t t, const Variant& v) {
   return (unsigned)std::max<int64_t>(1, std::min(g, total));
 }
 
+// The least steps that the batch's multi-step launches share (0: it has none).
+int64_t batch_fused_least(const lbm_cde* h) {
+  return h->batch_fuse.fuse < 2 ? 0 : h->batch_fuse.strip() ? 3 : 2 * h->batch_fuse.fuse;
+}
+
 // Whether steps t .. t + n of a batch may take the multi-step launch: it is
 // on, and no run's budget ends strictly inside the span.
 bool batch_fused_span(const lbm_cde* h, int64_t t, int64_t n) {
-  if (h->batch_fuse.fuse < 2 || n < (h->batch_fuse.strip() ? 3 : 2 * h->batch_fuse.fuse)) return false;
+  const int64_t least = batch_fused_least(h);
+  if (least == 0 || n < least) return false;
   for (const Run& r : h->runs) {
     const int64_t ms = r.d.max_steps;
     if (ms >= 0 && ms > t && ms < t + n) return false;
@@ -1838,13 +1845,14 @@ void advance_host_clock(lbm_cde* h, int64_t n) {
 int batch_step(lbm_cde* h, int64_t n) {
   int64_t done = 0;
   while (done < n) {
-    // a block of captured steps, or what is left of the call; where a run's
-    // budget ends inside it, the steps up to there
     const int gs = batch_graph_steps(h);
     const int64_t t = h->global_steps;
-    int64_t blk = std::min<int64_t>(n - done, gs);
-    for (const Run& r : h->runs)
-      if (r.d.max_steps > t) blk = std::min<int64_t>(blk, r.d.max_steps - t);
+    const int64_t blk = batch_block(n - done, gs, batch_fused_least(h), [&](int64_t s) {
+      int64_t end = INT64_MAX;
+      for (const Run& r : h->runs)
+        if (r.d.max_steps > t + s) end = std::min<int64_t>(end, r.d.max_steps - t);
+      return end;
+    });
     const unsigned grid = batch_grid_at(h, t);
     const bool fused = batch_fused_span(h, t, blk);
     const unsigned gridf = fused ? batch_fgrid_at(h, t, h->batch_fuse) : 0;
