@@ -2174,17 +2174,21 @@ void launch_fused_adj(const RunArgs& a, const char* v_hi, int64_t vstep, const v
 // two nodes per thread (FP64 58 x 10, whose 1024 nodes fill two 512-thread
 // blocks' LDS per CU), and four steps: at 512^2 small tiles' recomputed rings
 // cost more than they hide (FP32 2.81 ms against 2.66, FP64 5.16 and 3.98;
-// four concurrent conditions 11.0 and 7.5, 19.3 and 13.1).
+// four concurrent conditions 11.0 and 7.5, 19.3 and 13.1).  FP64 grids of 12 to
+// 15 rows, too low for that halo, take 60 x 8 and three steps (200 x 12, 200 steps
+// backward: 1.29 ms, one step per launch 2.14).
 struct AdjTile {
   int tx, ty, nth, T;
 };
-constexpr AdjTile kAdjSmall{16, 16, 960, 8}, kAdjLarge32{58, 16, 704, 4}, kAdjLarge64{58, 10, 512, 4};
+constexpr AdjTile kAdjSmall{16, 16, 960, 8}, kAdjLarge32{58, 16, 704, 4}, kAdjLarge64{58, 10, 512, 4},
+    kAdjLow64{60, 8, 384, 3};
 
 AdjTile adjoint_tile(const Run& r) {
   auto fits = [&](const AdjTile& t) { return !r.walls && fused_ok(r, Variant{t.tx, t.ty, 1, true, 0, 0, t.T}); };
   const AdjTile large = r.dbl ? kAdjLarge64 : kAdjLarge32;
   if (((r.d.nx + 15) / 16) * ((r.d.ny + 15) / 16) <= 256 && fits(kAdjSmall)) return kAdjSmall;
-  return fits(large) ? large : AdjTile{0, 0, 0, 0};
+  if (fits(large)) return large;
+  return r.dbl && fits(kAdjLow64) ? kAdjLow64 : AdjTile{0, 0, 0, 0};
 }
 
 template <int TX, int TY, int NTH, int STEPS>
@@ -2198,9 +2202,12 @@ void adjoint_dispatch(const Run& r, const AdjTile& t, Go go) {
   using Small = TileConst<kAdjSmall.tx, kAdjSmall.ty, kAdjSmall.nth, kAdjSmall.T>;
   using L32 = TileConst<kAdjLarge32.tx, kAdjLarge32.ty, kAdjLarge32.nth, kAdjLarge32.T>;
   using L64 = TileConst<kAdjLarge64.tx, kAdjLarge64.ty, kAdjLarge64.nth, kAdjLarge64.T>;
+  using Low = TileConst<kAdjLow64.tx, kAdjLow64.ty, kAdjLow64.nth, kAdjLow64.T>;
   if (t.T == kAdjSmall.T) {
     if (r.dbl) go(double(), Small());
     else go(float(), Small());
+  } else if (t.T == kAdjLow64.T) {
+    go(double(), Low());
   } else if (r.dbl) {
     go(double(), L64());
   } else {
