@@ -11,8 +11,8 @@ kernel, one adjoint gradient of the 512^2 inverse problem, the roofline of
 the dominant kernel and the FP64 CPU oracle timed on the host cores.
 
 Timing: after W warm-up steps each variant is timed in 5 blocks of at
-least K steps (a multiple of the library's 32-step captured graph, and at
-least 0.1 s), with HIP events on the stream the library launches on; the
+least K steps (a multiple of the library's captured graphs, and at least
+0.1 s), with HIP events on the stream the library launches on; the
 median per-step time is reported with the minimum and maximum.  The tuned
 variant of a run may take several steps per launch (LDS-blocked D2Q9); its
 launch is timed on its own (5 blocks of 40 back-to-back launches, median)
@@ -177,7 +177,7 @@ def log(msg):
     print(f"bench: {msg}", file=sys.stderr, flush=True)
 
 
-GRAPH_STEPS = 32               # steps per captured graph in the library
+GRAPH_STEPS = 96               # a multiple of the library's captured graphs: 48 steps of marching launches, else 32
 REPS = 5                       # timed blocks per variant (the median is reported)
 MIN_BLOCK_S = 0.1              # each timed block lasts at least this long
 
@@ -186,7 +186,7 @@ def time_blocks(advance, steps, warmup):
     """Seconds per step of ``advance(n)`` (enqueues n steps on torch's
     current stream, the stream the library launches on): after ``warmup``
     steps, REPS blocks are timed with HIP events, each a multiple of the
-    library's graph length (so long advances run as graph replays), at least
+    library's graph lengths (so long advances run as graph replays), at least
     ``steps`` steps and at least MIN_BLOCK_S long.  Returns the median, the
     minimum and maximum per-step time, the block length and the wall time."""
     import torch
@@ -295,8 +295,9 @@ def batch_variant(runs, precision, steps, warmup, tune=True):
     s.close()
     nodes = sum(r.nodes for r in runs)
     t_step = tm["median"]
-    # the runs have no budget, so a timed 32-step block is 32 / T launches of
-    # the (multi-step) batched kernel, each reading and writing every state once
+    # the runs have no budget, so a timed block is (nearly, where T does not
+    # divide a captured graph's steps into an even number) one launch per T steps
+    # of the (multi-step) batched kernel, each reading and writing every state once
     T = var.get("steps_per_launch", 1)
     bpl = BYTES_PER_LU[("d2q9", precision)]
     gbs = nodes * bpl / (T * t_step) / 1e9
@@ -644,8 +645,8 @@ def main():
         "timing": {"statistic": "median", "blocks": main_v["timed_blocks"],
                    "steps_per_block": main_v["steps_per_block"],
                    "ms_per_step_min_max": main_v["ms_per_step_min_max"],
-                   "note": "blocks are multiples of the 32-step captured graph, at least --steps steps and "
-                           "at least 0.1 s long, timed with HIP events on the library's stream"},
+                   "note": f"blocks are multiples of {GRAPH_STEPS} steps (captured graphs of 48 or 32), at least "
+                           "--steps steps and at least 0.1 s long, timed with HIP events on the library's stream"},
         "higher_is_better": True,
         "scaling": "weak",
         "vs_baseline": None,
