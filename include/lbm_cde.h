@@ -275,10 +275,12 @@ int lbm_cde_set_velocity(lbm_cde_handle h, int32_t run, const double* u);
  * minus one nodes on each side (nx and ny below 2^24, a population plane
  * below 4 GiB): the launch keeps the
  * intermediate steps of a tile and its halo in LDS (Eq. 5: a population
- * moves one node per step), so the state crosses HBM once per launch; the
- * steps left over when a call's count is not a multiple go one per launch.
+ * moves one node per step), so the state crosses HBM once per launch; of the
+ * steps left over when a call's count is not a multiple, four go together in
+ * 16 x 16 tiles where the launch takes more than four, the others one per launch.
  * Grids of up to 512 x 512 nodes have launches of their own: 8 x 64, 16 x 64
- * and 32 x 32 threads that take 8 steps of an 8 x 8, 16 x 16 or 32 x 32 tile,
+ * and 32 x 32 threads that take 8 steps of an 8 x 8, 16 x 16 or 32 x 32 tile
+ * (in FP64 32 x 16 where those are at most 256),
  * and 16 x 32 threads that take 4 of a 16 x 16 tile.  Runs of constant D and
  * constant or separable velocity with walls on both axes take 4 steps of a
  * 16 x 16 (16 x 32 threads) or 32 x 16 tile.  Blocks of 64 x 1 name
@@ -288,23 +290,28 @@ int lbm_cde_set_velocity(lbm_cde_handle h, int32_t run, const double* u);
  * nodes wide, periodic in y with at least 10 rows or bounded by walls; a
  * call's steps are divided evenly over launches of at most that many.
  * D3Q15 runs with a constant or separable velocity, periodic or mirrored in x
- * and y (any kind in z), take two steps per launch over blocks of columns that
- * march along z, and start so.
+ * and y (any kind in z), take two steps per launch over blocks of at most block x
+ * by block y columns, fewer on small or narrow grids, that march along z.
  * A run that can take several steps per launch starts with 4 (tiles of 64
  * columns and 24, 16 or, in FP64, 8 rows, by the tiles on the fullest CU), one
  * of at most 256 small tiles with the launch of the smallest such tile (4 steps
  * between 16,384 and 49,152 nodes and, for up to 512 tiles, with walls; else
- * 8), one of 600,000 nodes or more (300,000 in FP64) that can march, and a
- * batch of 100,000, with a marching launch of 4 to 6; any other with one.  A batched handle has
+ * 8).  A run that can march does so from 300,000 nodes on in FP64 and in FP32
+ * from 600,000, where a CU would take three 64 x 24 tiles (five between walls); a
+ * batch from as many nodes in all, unless budgets that end early would leave the
+ * launch half empty.  D3Q15 runs start with two steps, but for grids without walls
+ * of one row in y or of long rows that the caches hold (nx >= 400, 24 MB of
+ * state); any other run with one.  A batched handle has
  * one variant for all its runs; the run index only has to be valid.  Results
  * are bitwise the same for every variant. */
 
 /* Autotuner: time `trials` launches of every compiled variant (those listed
- * by lbm_cde_variant_at) and keep, per run, the one that takes a 32-step
- * block (the captured-graph length) in the least time, the steps a
- * multi-step variant leaves over going to the fastest one-step variant
- * (kept for them), or once for a batched handle the fastest.  Each timed launch reads the current state and overwrites
- * only the other population buffer, so the simulation state is unchanged.
+ * by lbm_cde_variant_at) and keep, per run, the one that takes a captured
+ * block (32 steps, or 48 of marching launches) in the least time per step, the
+ * steps a multi-step variant leaves over going to the fastest one-step variant
+ * (kept for them), or once for a batched handle the fastest.  Each timed launch
+ * reads the current state and overwrites only the other population buffer, so
+ * the simulation state is unchanged.
  * If the environment variable LBM_CDE_TUNE_CACHE names a file, results are
  * looked up there (keyed by GPU architecture, lattice, precision, grid and
  * boundaries, and for a batch by every run's grid, boundaries and budget)

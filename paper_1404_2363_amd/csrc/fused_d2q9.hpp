@@ -400,11 +400,13 @@ LBM_FORCEINLINE void fused_tile(const RunArgs& a, uint32_t txi, uint32_t tyi, ch
     __syncthreads();
   }
 
-  // step T: LDS -> HBM for the tile's own nodes.  Streaming stores where rows
-  // are whole cache lines (600 x 480 FP32 in 64 x 24 tiles: 2.40 us a step,
-  // stored plainly 2.56) or the state is small; 32-node rows start and end
-  // inside lines that the caches should gather (512^2 in 32 x 32 tiles: FP32
-  // 2.05 us streamed, 1.99 plainly, FP64 3.00 and 2.92).
+  // step T: LDS -> HBM for the tile's own nodes.  32-wide tiles store plainly and
+  // the others stream, as measured, us a step streamed and plainly: 32 x 32 at
+  // 512^2 FP32 2.05 and 1.99, FP64 3.00 and 2.92; 64 x 24 at 600 x 480 FP32 2.40
+  // and 2.56; 8 x 8 at 128^2 0.861 and 0.862; 16 x 16 at 256^2 1.106 and 1.105,
+  // FP64 1.43 and 1.45; between walls on both axes 16 x 16 is open (600 x 480 FP32
+  // 2.98 and 3.11, FP64 4.61 and 4.26; 512 x 768 4.10 and 3.95, 5.19 and 5.09).
+  constexpr bool STREAM = !VOUT && TX != 32;
   // the nine destination planes as scalar base addresses (the empty asm keeps
   // each in scalar registers and out of the per-node address arithmetic, so
   // a store takes the base-plus-32-bit-offset form with no vector add)
@@ -426,7 +428,7 @@ LBM_FORCEINLINE void fused_tile(const RunArgs& a, uint32_t txi, uint32_t tyi, ch
     if (VOUT && !store_end) continue;
     const uint32_t off = (__umul24((uint32_t)y, (uint32_t)nx) + x) * (uint32_t)sizeof(R);
 #pragma unroll
-    for (int i = 0; i < 9; ++i) gst<R, !VOUT && TX != 32>(dpl[i], off, g[i]);
+    for (int i = 0; i < 9; ++i) gst<R, STREAM>(dpl[i], off, g[i]);
   }
 }
 

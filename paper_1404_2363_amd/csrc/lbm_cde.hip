@@ -123,7 +123,7 @@ struct Run {
   bool walls = false;
   VolCut vol[2] = {};  // D3Q15, two steps per launch: the cut over each of kVolTiles
   Variant var{256, 1, 1, true, false};
-  Variant var4{256, 1, 1, true, false};  // four-step launches for what an eight-step variant leaves over
+  Variant var4{256, 1, 1, true, false};  // four-step launches for what a variant of more steps leaves over
   Variant var1{256, 1, 1, true, false};  // one-step launches (the steps a multi-step variant leaves over)
 };
 
@@ -837,7 +837,10 @@ Variant small_variant(int k, int xcd = 1) {
 // 49,152 nodes (192 tiles of 16 x 16) runs keep four steps, in 16 x 16 tiles
 // (1.2 us at 128^2 FP32), as do those with walls up to two tiles per CU
 // (400 x 300, 475 tiles: FP32 1.91 us a step, 64 x 16 tiles 2.42; FP64 2.30
-// and, 64 x 8 tiles, 3.31; from three tiles per CU on the large ones win).
+// and, 64 x 8 tiles, 3.31; from three tiles per CU on the large ones win).  A
+// velocity field, which every step reads, changes nothing: 128^2 2.74 and 1.01
+// (FP64 2.66 and 1.16), 256^2 2.85 and 1.29 (2.75 and 1.58), 300^2 FP64 2.81 and
+// 2.14, 512^2 3.24 and 2.40 (4.39 and 3.28).
 Variant small_start(const Run& r, const Variant& other);
 
 // The marching launch takes the runs of the tile kernel with a constant D, a
@@ -1030,8 +1033,11 @@ std::vector<int> strip_split(int64_t n, int T, int parity) {
 }
 
 // Enqueue n steps of run r (fewer where its budget ends first): launches of
-// its variant while they fit, one-step launches for the rest.  With `even`,
-// one multi-step launch is traded for one-step launches where that makes the
+// its variant while they fit, for the rest four-step ones in 16 x 16 tiles where
+// the variant takes more (four steps that way against one at a time: 700 x 600
+// 13-16 us and 37, 4096^2 455 and 812; a captured block leaves none over) and
+// one-step launches; marching launches share the steps.  With `even`, one
+// multi-step launch is traded for one-step launches where that makes the
 // number of launches even (a captured graph must leave the state in the
 // buffer it started from).  Returns the number of launches.
 int64_t enqueue_run(lbm_cde* h, Run& r, int64_t n, hipStream_t s, bool even = false) {
@@ -1605,7 +1611,7 @@ int init_runs(lbm_cde* h, const lbm_cde_run_desc* runs, int32_t nruns, const dou
         const Variant tile = r.d.bc[0] == LBM_CDE_PERIODIC ? tile_start(r) : box_start(r);
         if (find_step(r, tile)) r.var = small_start(r, tile);
         else r.var = small_start(r, r.var);
-        // what an eight-step launch leaves over goes in 16 x 16 tiles
+        // what a launch of more than four steps leaves over goes in 16 x 16 tiles
         r.var4 = find_step(r, small_variant(3)) ? small_variant(3) : r.var1;
       }
       const Variant march = strip_start(r);
