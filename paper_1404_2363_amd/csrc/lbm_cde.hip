@@ -1493,11 +1493,20 @@ double batch_strip_loss(const lbm_cde* h, const StripCut& c) {
 // and 5.7, two (1.38) 4.3 and 3.9; between walls six channels of 4096 x 64 .. 104,
 // one ending early (1.14) 11.0 and 9.3, 64 channels, half of them ending early
 // (1.18) 27 and 32.
+// Channels of uneven heights, cut by the tallest, march in FP32 from 1,500,000
+// nodes on (32 .. 128 rows, us a step, march and tiles: 6 of 1723 columns, 689k
+// nodes, 6.6-9.1 and 5.5; 18 of 850, 1061k, 9.5-11.0 and 8.7; 25 of 850, 1564k,
+// 11.4 and 11.6; 33 rows each, 13 of 1723, 739k, 6.2 and 7.5).
 Variant batch_strip_start(const lbm_cde* h, bool tiles) {
   const Run& r0 = h->runs[0];
   const bool walls = r0.d.bc[1] != LBM_CDE_PERIODIC;
-  int64_t nodes = 0;
-  for (const Run& r : h->runs) nodes += r.nodes;
+  int64_t nodes = 0, low = r0.d.ny, tall = r0.d.ny;
+  for (const Run& r : h->runs) {
+    nodes += r.nodes;
+    low = std::min<int64_t>(low, r.d.ny);
+    tall = std::max<int64_t>(tall, r.d.ny);
+  }
+  const int64_t least = tiles && !r0.dbl && walls && 4 * low < 3 * tall ? 1500000 : strip_nodes(r0.dbl);
   StripCut best{1, 0, 1e300};
   for (int T = 4; T <= kStripMax; ++T) {
     int64_t lanes = 0, kept = 0;
@@ -1505,7 +1514,7 @@ Variant batch_strip_start(const lbm_cde* h, bool tiles) {
       lanes += (r.d.nx + strip_width(T) - 1) / strip_width(T) * 64;
       kept += r.d.nx;
     }
-    if (nodes < strip_nodes(r0.dbl) || 10 * kept < 7 * lanes || !find_batch_fused(h, strip_variant(T))) continue;
+    if (nodes < least || 10 * kept < 7 * lanes || !find_batch_fused(h, strip_variant(T))) continue;
     const StripCut c = strip_cut_batch(h, T);
     if (c.cost < best.cost) best = c;
   }

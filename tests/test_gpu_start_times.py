@@ -88,3 +88,21 @@ def test_batch_whose_runs_end(precision, nx, ny, nruns, ending, marches):
     for s in runs:
         s.close()
     assert start <= 1.05 * tiles
+
+
+@pytest.mark.parametrize("nx,heights,marches", [
+    (1723, (32, 48, 64, 96, 128, 32), False), (850, (32, 48, 64, 96, 128) * 3, False), (1723, (33,) * 13, True),
+])
+def test_batch_of_channels(nx, heights, marches):
+    """FP32 channels of uneven heights start with tiles below 1,500,000 nodes."""
+    from paper_1404_2363_amd.solver import Solver
+    wls = [_workload(nx, ny, "walls")[0] for ny in heights]
+    runs = [Solver(wls, "fp32") for _ in range(2)]
+    assert (runs[0].variant()["block"] == (64, 1)) == marches
+    runs[1].set_variant({"block": T24[:2], "rows_per_thread": T24[2], "nt_stores": True, "block_order": 0, "grid": 0,
+                         "steps_per_launch": 4})
+    start, tiles = _best(runs)
+    print(f"case channels {len(heights)} x {nx}: {start * 1e6:.0f} us, tiles {tiles * 1e6:.0f} us", flush=True)
+    for s in runs:
+        s.close()
+    assert start <= 1.05 * tiles
