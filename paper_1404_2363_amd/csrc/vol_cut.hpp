@@ -29,30 +29,37 @@ struct VolCut {
 // chunk a part of its own (two barriers and the latency of the pull), one per
 // wave and one per cache line of the pull that the CU has to serve, for the k
 // blocks that run on it at once.  Blocks share a CU as its LDS and registers
-// allow; a started round of blocks costs most of a full one.  States past the
-// 256 MB memory-side cache wait longer for their planes and are bound by 5.6
-// TB/s as well, of which the re-read halo takes a part; there a smaller tile
-// gains nothing.
+// allow; a started round of blocks costs most of a full one.
+// States past the 256 MB memory-side cache wait longer for their planes and are
+// bound by memory as well, of which the re-read halo takes a part: the constants
+// of a fit of their own, to 3978 cuts of 28 grids up to 256^3 (the best cut by it
+// is 1.4 % off the best one measured, 25 % at most).  Cut into even shares, they
+// have no block that is mostly padding: 110 x 200 x 140 FP64 in 28 x 13 columns
+// 82 us a step, 107 in 32 x 13; 150^3 93 in 30 columns and 109 in 32.
 // 256^3: 64 x 8 197 us a step and 32 x 16 208, which re-reads more lines; FP64
 // 32 x 8 407 and 32 x 13 433 (1.9 rounds of blocks); 101 x 90 x 77 FP64 32 x 13
 // 19.4, 32 x 8 22.  Between z walls alone (wz) the FP64 kernel takes every
 // register, and its planes of 6 waves come slower (128^3 67 us, 32 x 13 59).
 inline VolCut vol_cut(int bx, int by, bool dbl, bool wz, int64_t nx, int64_t ny, int64_t nz) {
   const int64_t E = dbl ? 8 : 4, max_waves = dbl ? 8 : 12, lds = 15 * E * (bx + 2) * (by + 2);
-  const double fixed = dbl ? 3.2 : 3.0, plane = dbl ? 1.1 : 1.0, wave = dbl ? 0.19 : 0.07, line = dbl ? 0.008 : 0.0085;
   const double bytes = (double)nx * (double)ny * (double)nz * 30.0 * (double)E;
   const bool cached = bytes <= 256e6;
-  // whole tiles; cut down also their halves and quarters, and even shares of the
-  // grid (along x, where rows then start inside a line, if that saves a sixteenth
-  // of the columns: 400 x 30 x 30 FP32 9.4 us a step in 31 columns, 9.0 in 32)
+  const double fixed = dbl ? 3.2 : 3.0;
+  const double plane = cached ? (dbl ? 1.1 : 1.0) : (dbl ? 0.53 : 0.51);
+  const double wave = cached ? (dbl ? 0.19 : 0.07) : (dbl ? 0.34 : 0.079);
+  const double line = cached ? (dbl ? 0.008 : 0.0085) : (dbl ? 0.037 : 0.044);
+  // whole tiles and even shares of the grid (along x, where rows then start inside
+  // a line, if that saves a sixteenth of the columns: 400 x 30 x 30 FP32 9.4 us a
+  // step in 31 columns, 9.0 in 32); of cached states halves and quarters too, which
+  // give small grids more blocks
   const int64_t ex = (nx + bx - 1) / bx, ey = (ny + by - 1) / by;
   const int64_t share = 16 * (ex * bx - nx) > nx ? (nx + ex - 1) / ex : bx;
   VolCut best{bx, by, (int32_t)nz, 1e300};
   for (int64_t tx : {(int64_t)bx, (int64_t)bx / 2, (int64_t)bx / 4, (int64_t)8, share}) {
-    if (!cached && tx != bx) break;
+    if (!cached && tx != bx && tx != share) continue;
     tx = std::min(tx, nx);
     for (int64_t ty : {(int64_t)by, (int64_t)by / 2, (int64_t)by / 4, (ny + ey - 1) / ey, (ny + 2 * ey - 1) / (2 * ey)}) {
-      if (!cached && ty != by) break;
+      if (!cached && ty != by && ty != (ny + ey - 1) / ey) continue;
       ty = std::min(ty, ny);
       const int64_t tiles = (nx + tx - 1) / tx * ((ny + ty - 1) / ty), w = ((tx + 2) * (ty + 2) + 63) / 64;
       const double lines = (double)((ty + 2) * ((tx * E + 127) / 128 + (tx * E % 128 == 0 ? 2 : 1)));
@@ -68,10 +75,10 @@ inline VolCut vol_cut(int bx, int by, bool dbl, bool wz, int64_t nx, int64_t ny,
         const double rounds = q <= 1.0 ? 1.0 : std::max(q + 0.15, std::ceil(q) - 0.3);
         double t = rounds * (double)(L + 2) * (plane + std::min(cap, std::ceil(n)) * (wave * (double)w + line * lines));
         if (!cached) {
-          const double halo = 1.0 + 0.075 * (lines * 128.0 / (double)(tx * ty * E) - 1.0);
-          t = std::max(1.25 * t, bytes * halo * (double)(L + 3) / (double)L / 5.6e6 * (q > 1.0 ? rounds / q : 1.0));
+          const double halo = 1.0 + (dbl ? 0.25 : 0.145) * (lines * 128.0 / (double)(tx * ty * E) - 1.0);
+          t = std::max(t, bytes * halo * (double)(L + 3) / (double)L / (dbl ? 5.4e6 : 6.0e6) * (q > 1.0 ? rounds / q : 1.0));
         }
-        t = (fixed + t) * (wz && dbl && by == 8 ? 1.114 : 1.0);
+        t = (fixed + t) * (wz && dbl && by == 8 ? (cached ? 1.114 : 1.145) : 1.0);
         if (t < best.cost) best = VolCut{(int32_t)tx, (int32_t)ty, (int32_t)L, t};
       }
     }

@@ -73,6 +73,15 @@ def test_small_and_thin_grids_are_cut(cut):
     assert [r[1] for r in cut(list(one_step))] == list(one_step.values())
 
 
+def test_large_grids_have_even_shares(cut):
+    # states past the memory-side cache whose last column of tiles would be mostly padding
+    for grid, dbl, first, shape in [((110, 200, 140), 1, (32, 13), (28, 13)), ((110, 200, 140), 0, (64, 8), (55, 8)),
+                                    ((150, 150, 150), 1, (32, 13), (30, 13)), ((66, 66, 600), 1, (32, 13), (22, 11)),
+                                    ((192, 192, 192), 0, (64, 8), (64, 8)), ((256, 256, 256), 1, (32, 8), (32, 8))]:
+        k, one, cuts = cut([(grid, dbl)])[0]
+        assert TILES[dbl][k] == first and not one and cuts[k][:2] == shape, (grid, dbl, cuts)
+
+
 def test_bounds(cut):
     import random
     rng = random.Random(5)
