@@ -20,9 +20,12 @@
 // What bounds it: vector instructions (512^2 FP32, four steps: a third of a
 // launch's 13 us alone, two thirds when other launches fill its start and
 // end).  A thread therefore keeps the same nodes for all T steps, with their
-// coordinates, flux block, velocity and gradient sums in registers (per step
-// and node 126 vector instructions, 210 with new coordinates and reads at
-// every step), and v of the next step is read while the current one computes.
+// coordinates, flux block, velocity and gradient sums in registers, and v of
+// the next step is read while the current one computes.  Vector instructions
+// per node and step, recomputed rings included: reverse 189, 223 with new
+// coordinates and reads at every step and a 64 x 16 tile; recomputation 199 and
+// 193 (the smaller tile has more of a ring).  Four steps of 2048^2: reverse
+// 180 -> 151 us, recomputation 133 -> 131.
 // mu, the sums and the recomputed states are stored plainly, since the next
 // launch reads them from the caches; v, read back after the whole segment,
 // bypasses them.  Four conditions at 512^2, 400 steps backward: FP32 9.3 ms

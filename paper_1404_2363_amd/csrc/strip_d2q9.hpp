@@ -21,13 +21,15 @@
 // What bounds it, MI355X, 4096^2: the LDS tile kernel (fused_d2q9.hpp) issues
 // 134 VALU instructions per node and step (addressing and the recomputed
 // rings of a 64 x 24 tile on top of the collision's 93) and waits at two
-// barriers per step; the march issues 99 and recomputes 64 / 54 columns and
-// T - 1 rows per chunk.  A launch moves the state once whatever T is, which
-// takes 280-290 us in FP32 for T = 3 and 4 (4.2 TB/s: 9 + 9 row streams per
-// wave), 310 for T = 5 and 350 for T = 6, where the VALU is the bound (86 %
-// of its issue rate): T = 6 gives 59 us a step against 69-75 for the tile
-// kernel on the same GPU (FP64: 98 against 152; at 2048^2 16.7 against 20.1,
-// FP64 27 against 40).  T = 8 keeps 50 columns of 64 and was 4-10 % slower.
+// barriers per step; the march issues 99 for a node that it computes, 121 per
+// node and step with the 64 / 54 columns and T - 1 rows per chunk that it
+// recomputes.  A launch moves the state once whatever T is, which takes 280-290
+// us in FP32 for T = 3 and 4 (4.2 TB/s: 9 + 9 row streams per wave), 310 for
+// T = 5 and 348 for T = 6, where the VALU is the bound (1.9e8 wave instructions,
+// 89 % of its issue rate; 1.32 GB, 1.09 times the state): T = 6 gives 58 us a step
+// against 69-75 for the tile kernel on the same GPU (FP64: 98 against 152; at
+// 2048^2 16.7 against 20.1, FP64 27 against 40).  T = 8 keeps 50 columns of 64
+// and was 4-10 % slower.
 // 64 channels of 32-128 rows in a batch x 400 sampled steps: 39.4 to 28.8 ms;
 // 12 plate channels in FP64 x 200: 5.4 to 3.5 ms.
 // Plain stores: the rows end inside a cache line that the neighbouring wave
