@@ -291,15 +291,16 @@ int lbm_cde_set_velocity(lbm_cde_handle h, int32_t run, const double* u);
  * call's steps are divided evenly over launches of at most that many.
  * D3Q15 runs with a constant or separable velocity, periodic or mirrored in x
  * and y (any kind in z), take two steps per launch over blocks of at most block x
- * by block y columns, fewer on small or narrow grids, that march along z.
+ * by block y columns, fewer on small grids and where even shares of the grid
+ * leave less padding, that march along z.
  * A run that can take several steps per launch starts with 4 (tiles of 64
  * columns and 24, 16 or, in FP64, 8 rows, by the tiles on the fullest CU), one
  * of at most 256 small tiles with the launch of the smallest such tile (4 steps
  * between 16,384 and 49,152 nodes and, for up to 512 tiles, with walls; else
  * 8).  A run that can march does so from 300,000 nodes on in FP64 and in FP32
  * from 600,000, where a CU would take three 64 x 24 tiles (five between walls); a
- * batch from as many nodes in all, unless budgets that end early would leave the
- * launch half empty.  D3Q15 runs start with two steps, but for grids without walls
+ * batch from as many nodes in all (FP32 channels of uneven heights 1,500,000),
+ * unless budgets that end early would leave the launch half empty.  D3Q15 runs start with two steps, but for grids without walls
  * of one row in y or of long rows that the caches hold (nx >= 400, 24 MB of
  * state); any other run with one.  A batched handle has
  * one variant for all its runs; the run index only has to be valid.  Results
