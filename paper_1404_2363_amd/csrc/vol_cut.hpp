@@ -33,7 +33,8 @@ struct VolCut {
 // States past the 256 MB memory-side cache wait longer for their planes and are
 // bound by memory as well, of which the re-read halo takes a part: the constants
 // of a fit of their own, to 3978 cuts of 28 grids up to 256^3 (the best cut by it
-// is 1.4 % off the best one measured, 25 % at most).  Cut into even shares, they
+// is 0.8 % off the best one measured, 17 % at most; in FP32 a row cut inside a line
+// counts a line more there than in cached grids).  Cut into even shares, they
 // have no block that is mostly padding: 110 x 200 x 140 FP64 in 28 x 13 columns
 // 82 us a step, 107 in 32 x 13; 150^3 93 in 30 columns and 109 in 32.
 // 256^3: 64 x 8 197 us a step and 32 x 16 208, which re-reads more lines; FP64
@@ -45,9 +46,9 @@ inline VolCut vol_cut(int bx, int by, bool dbl, bool wz, int64_t nx, int64_t ny,
   const double bytes = (double)nx * (double)ny * (double)nz * 30.0 * (double)E;
   const bool cached = bytes <= 256e6;
   const double fixed = dbl ? 3.2 : 3.0;
-  const double plane = cached ? (dbl ? 1.1 : 1.0) : (dbl ? 0.53 : 0.51);
-  const double wave = cached ? (dbl ? 0.19 : 0.07) : (dbl ? 0.34 : 0.079);
-  const double line = cached ? (dbl ? 0.008 : 0.0085) : (dbl ? 0.037 : 0.044);
+  const double plane = cached ? (dbl ? 1.1 : 1.0) : (dbl ? 0.53 : 0.87);
+  const double wave = cached ? (dbl ? 0.19 : 0.07) : (dbl ? 0.34 : 0.07);
+  const double line = cached ? (dbl ? 0.008 : 0.0085) : (dbl ? 0.037 : 0.0365);
   // whole tiles and even shares of the grid (along x, where rows then start inside
   // a line, if that saves a sixteenth of the columns: 400 x 30 x 30 FP32 9.4 us a
   // step in 31 columns, 9.0 in 32); of cached states halves and quarters too, which
@@ -62,7 +63,7 @@ inline VolCut vol_cut(int bx, int by, bool dbl, bool wz, int64_t nx, int64_t ny,
       if (!cached && ty != by && ty != (ny + ey - 1) / ey) continue;
       ty = std::min(ty, ny);
       const int64_t tiles = (nx + tx - 1) / tx * ((ny + ty - 1) / ty), w = ((tx + 2) * (ty + 2) + 63) / 64;
-      const double lines = (double)((ty + 2) * ((tx * E + 127) / 128 + (tx * E % 128 == 0 ? 2 : 1)));
+      const double lines = (double)((ty + 2) * ((tx * E + 127) / 128 + (tx * E % 128 == 0 || (!cached && !dbl) ? 2 : 1)));
       // blocks of more than a wave per SIMD take whole rows of the four SIMDs
       const double cap = (double)std::max<int64_t>(
           1, std::min<int64_t>(160 * 1024 / lds, max_waves / (w <= 4 ? w : (w + 3) / 4 * 4)));
@@ -75,8 +76,8 @@ inline VolCut vol_cut(int bx, int by, bool dbl, bool wz, int64_t nx, int64_t ny,
         const double rounds = q <= 1.0 ? 1.0 : std::max(q + 0.15, std::ceil(q) - 0.3);
         double t = rounds * (double)(L + 2) * (plane + std::min(cap, std::ceil(n)) * (wave * (double)w + line * lines));
         if (!cached) {
-          const double halo = 1.0 + (dbl ? 0.25 : 0.145) * (lines * 128.0 / (double)(tx * ty * E) - 1.0);
-          t = std::max(t, bytes * halo * (double)(L + 3) / (double)L / (dbl ? 5.4e6 : 6.0e6) * (q > 1.0 ? rounds / q : 1.0));
+          const double halo = 1.0 + (dbl ? 0.25 : 0.083) * (lines * 128.0 / (double)(tx * ty * E) - 1.0);
+          t = std::max(t, bytes * halo * (double)(L + 3) / (double)L / (dbl ? 5.4e6 : 5.6e6) * (q > 1.0 ? rounds / q : 1.0));
         }
         t = (fixed + t) * (wz && dbl && by == 8 ? (cached ? 1.114 : 1.145) : 1.0);
         if (t < best.cost) best = VolCut{(int32_t)tx, (int32_t)ty, (int32_t)L, t};

@@ -82,6 +82,14 @@ def test_large_grids_have_even_shares(cut):
         assert TILES[dbl][k] == first and not one and cuts[k][:2] == shape, (grid, dbl, cuts)
 
 
+def test_large_fp32_start_tile(cut):
+    # where the two tiles lie close, and even shares of 64 columns save no line of the pull
+    for grid in [(160, 160, 160), (220, 90, 200), (150, 150, 150), (90, 300, 100)]:
+        assert TILES[0][cut([(grid, 0)])[0][0]] == (32, 16), grid
+    for grid in [(192, 192, 192), (144, 144, 144), (300, 300, 90), (512, 256, 64)]:
+        assert TILES[0][cut([(grid, 0)])[0][0]] == (64, 8), grid
+
+
 def test_bounds(cut):
     import random
     rng = random.Random(5)
